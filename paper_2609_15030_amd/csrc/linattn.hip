@@ -396,7 +396,7 @@ la_status launch_fused(const PrefillCall &c, const WsPlan &p, int64_t max_chunks
         } else if constexpr (DK == 128 && DV == 128) {
             sa.n_narrow = (int32_t)sw.n_narrow;
             const int64_t blocks = 4 * sw.n_narrow + 16 * ((pairs - sw.n_narrow + 7) / 8);
-            hipLaunchKernelGGL((la::gdr_xscan_mixed_kernel<DK, DV>), dim3((unsigned)blocks), dim3(384), 0, c.stream, sa);
+            hipLaunchKernelGGL((la::gdr_xscan_mixed_kernel<DK, DV>), dim3((unsigned)blocks), dim3(512), 0, c.stream, sa);
             if (la_status e = hip_check("fused scan launch")) return e;
         }
     }
