@@ -40,10 +40,10 @@ struct XPrepArgs {
     const void *k;
     const float *g, *beta;
     const int32_t *cu;
-    int32_t n_seqs, n_heads, C, cps, variant, max_chunks;
+    int32_t n_heads, C, cps, variant;
     uint4 *misc;       // per slot-head: X diag(beta) fragments [kXFrags][64 lanes] x 16 B,
                        // then the gate block [4][64] fp32: G, exp(Gp), beta, exp(G_63 - G)
-    int32_t chunk_major;
+    UnitMap map;           // the block's unit (see unit_of_block)
 };
 
 // A and X are unit-lower-triangular: only their ten 16x16 blocks (bi, bj),
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void gdr_xprep_kernel(XPrepArgs a) {
     const int g16 = lane >> 4, c16 = lane & 15;
     int64_t j;
     int seq, h;
-    if (!unit_of_block(a.n_seqs, a.n_heads, a.max_chunks, a.chunk_major != 0, &seq, &h, &j)) return;
+    if (!unit_of_block(a.map, a.cu, &seq, &h, &j)) return;
     const int H = a.n_heads;
     const int64_t cu0 = a.cu[seq];
     const int len = a.cu[seq + 1] - a.cu[seq];

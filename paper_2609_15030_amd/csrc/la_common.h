@@ -191,52 +191,96 @@ __device__ __host__ inline int64_t total_slots(int64_t total_tokens, int64_t n_s
 //   pair-major: (sequence, head) pair p goes to XCD p % 8, as in the scan
 //     kernels, so a chain's chunks are prepared where it is scanned;
 //     block id = 8 * (chunk + max_chunks * (p / 8)) + p % 8;
-//   chunk-major: the units of chunk c of a sequence, for every head, go to
-//     XCD c % 8, so the chunk's gates and betas (stored [token, head]: a
-//     cache line holds a few tokens of every head) are fetched once into one
-//     L2 rather than once per head into several; block id =
-//     8 * ((seq * CG + c / 8) * H + head) + c % 8, CG = ceil(max_chunks / 8).
-// The host takes chunk-major for launches of many units, where the gathers'
+//   slot-major: the units of workspace slot t (a chunk of some sequence; see
+//     slot_base), for every head, go to XCD t % 8, so the chunk's gates and
+//     betas (stored [token, head]: a cache line holds a few tokens of every
+//     head) are fetched once into one L2 rather than once per head into
+//     several; block id = 8 * ((t / 8) * H + head) + t % 8.  Slots exist for the
+//     chunks there are (one spare per sequence at most), so a batch of uneven or
+//     short sequences launches no blocks for chunks it does not have and
+//     loads all XCDs alike: with a slot per (sequence, chunk number) instead, 64
+//     prompts of 1 to 300 tokens used five XCDs of eight (26 us for the
+//     preparation).
+// The host takes slot-major for launches of many units, where the gathers'
 // traffic counts, and pair-major otherwise.
 // ---------------------------------------------------------------------------
-constexpr int64_t kChunkMajorUnits = 2048;
+constexpr int64_t kSlotMajorUnits = 2048;
 
-__host__ inline bool chunk_major_map(int n_seqs, int n_heads, int64_t max_chunks) {
-    return (int64_t)n_seqs * n_heads * max_chunks > kChunkMajorUnits;
+__host__ inline bool slot_major_map(int n_seqs, int n_heads, int64_t max_chunks) {
+    return (int64_t)n_seqs * n_heads * max_chunks > kSlotMajorUnits;
 }
 
-__device__ inline bool unit_of_block(int n_seqs, int n_heads, int max_chunks, bool chunk_major, int *seq,
-                                     int *head, int64_t *chunk) {
+// The sequence owning workspace slot t: the last one whose slot base is at
+// most t (bases never decrease, and an empty sequence's base equals the
+// next one's or is a spare slot's).  base_i <= t is tested without its
+// division, as cu_i cps + (C - 1) i < (t + 1) C: halving down to 64
+// sequences, then one comparison per lane.  Every wave of the block computes it.
+__device__ inline int seq_of_slot(const int32_t *cu, int n_seqs, uint32_t t, int C, int cps) {
+    const uint64_t lim = ((uint64_t)t + 1) * (uint64_t)(uint32_t)C;
+    auto below = [&](int i) {
+        return (uint64_t)(uint32_t)cu[i] * (uint32_t)cps + (uint64_t)(uint32_t)(C - 1) * (uint32_t)i < lim;
+    };
+    int lo = 0, n = n_seqs;              // base_lo <= t; the owner is in [lo, lo + n)
+    while (n > kWave) {
+        const int half = n >> 1;
+        if (below(lo + half)) {
+            lo += half;
+            n -= half;
+        } else {
+            n = half;
+        }
+    }
+    const int lane = threadIdx.x & 63;
+    const bool in = lane < n && below(lo + (lane < n ? lane : 0));
+    return lo + __popcll(__ballot(in)) - 1;
+}
+
+struct UnitMap {
+    int32_t n_seqs, n_heads, C, cps, max_chunks;
+    int32_t slots;         // slot-major: workspace slots; 0: pair-major
+};
+
+__device__ inline bool unit_of_block(const UnitMap &u, const int32_t *cu, int *seq, int *head, int64_t *chunk) {
     // 32-bit arithmetic: a 64-bit division costs hundreds of cycles at the
     // start of every workgroup (grids stay below 2^32)
     const uint32_t b = blockIdx.x;
     const uint32_t x = b & 7, m = b >> 3;
-    const uint32_t H = (uint32_t)n_heads;
-    uint32_t sq, hd, c;
-    if (chunk_major) {
-        const uint32_t CG = ((uint32_t)max_chunks + 7) / 8;
-        const uint32_t t = m / H;
-        hd = m - t * H;
-        sq = t / CG;
-        c = 8 * (t - sq * CG) + x;
-        if (sq >= (uint32_t)n_seqs || c >= (uint32_t)max_chunks) return false;
-    } else {
-        const uint32_t q = m / (uint32_t)max_chunks;
-        const uint32_t pair = x + 8 * q;
-        if (pair >= (uint32_t)n_seqs * H) return false;
-        c = m - q * (uint32_t)max_chunks;
-        sq = pair / H;
-        hd = pair - sq * H;
+    const uint32_t H = (uint32_t)u.n_heads;
+    if (u.slots > 0) {
+        const uint32_t q = m / H, t = 8 * q + x;
+        if (t >= (uint32_t)u.slots) return false;
+        const int sq =
+            u.n_seqs == 1 ? 0 : __builtin_amdgcn_readfirstlane(seq_of_slot(cu, u.n_seqs, t, u.C, u.cps));
+        *seq = sq;
+        *head = (int)(m - q * H);
+        *chunk = (int64_t)t - slot_base_dev(cu[sq], sq, u.C, u.cps);
+        return true;
     }
-    *seq = (int)sq;
-    *head = (int)hd;
-    *chunk = (int64_t)c;
+    const uint32_t q = m / (uint32_t)u.max_chunks;
+    const uint32_t pair = x + 8 * q;
+    if (pair >= (uint32_t)u.n_seqs * H) return false;
+    *chunk = (int64_t)(m - q * (uint32_t)u.max_chunks);
+    *seq = (int)(pair / H);
+    *head = (int)(pair - (pair / H) * H);
     return true;
 }
 
+// Blocks of a launch over every (sequence, head, chunk number), the bound a
+// call is checked against, and blocks of the launch itself.
 __host__ inline int64_t chunk_grid_blocks(int n_seqs, int n_heads, int64_t max_chunks) {
-    if (chunk_major_map(n_seqs, n_heads, max_chunks)) return 8 * ((max_chunks + 7) / 8) * (int64_t)n_seqs * n_heads;
+    if (slot_major_map(n_seqs, n_heads, max_chunks)) return 8 * ((max_chunks + 7) / 8) * (int64_t)n_seqs * n_heads;
     return 8 * max_chunks * (((int64_t)n_seqs * n_heads + 7) / 8);
+}
+
+__host__ inline UnitMap unit_map(int n_seqs, int n_heads, int C, int cps, int64_t max_chunks, int64_t total_tokens) {
+    const int64_t slots =
+        slot_major_map(n_seqs, n_heads, max_chunks) ? total_slots(total_tokens, n_seqs, C, cps) : 0;
+    return UnitMap{n_seqs, n_heads, C, cps, (int32_t)max_chunks, (int32_t)slots};
+}
+
+__host__ inline int64_t unit_map_blocks(const UnitMap &u) {
+    if (u.slots > 0) return 8 * (((int64_t)u.slots + 7) / 8) * u.n_heads;
+    return chunk_grid_blocks(u.n_seqs, u.n_heads, u.max_chunks);
 }
 
 // ---------------------------------------------------------------------------

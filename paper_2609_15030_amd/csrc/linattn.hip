@@ -357,10 +357,10 @@ la_status launch_fused(const PrefillCall &c, const WsPlan &p, int64_t max_chunks
     trace_mark(0, c.stream);
     (void)hipGetLastError();
     if (max_chunks > 0) {
-        la::XPrepArgs pa{c.k, c.g, c.beta, c.cu_dev, s->n_seqs, s->n_heads, s->ckpt_interval, cps, s->variant,
-                         (int32_t)max_chunks, ws.misc,
-                         la::chunk_major_map(s->n_seqs, s->n_heads, max_chunks) ? 1 : 0};
-        const int64_t blocks = la::chunk_grid_blocks(s->n_seqs, s->n_heads, max_chunks);
+        const la::UnitMap map = la::unit_map(s->n_seqs, s->n_heads, s->ckpt_interval, cps, max_chunks,
+                                             c.cu_host[s->n_seqs]);
+        la::XPrepArgs pa{c.k, c.g, c.beta, c.cu_dev, s->n_heads, s->ckpt_interval, cps, s->variant, ws.misc, map};
+        const int64_t blocks = la::unit_map_blocks(map);
         hipLaunchKernelGGL((la::gdr_xprep_kernel<DK>), dim3((unsigned)blocks), dim3(256), 0, c.stream, pa);
         if (la_status e = hip_check("chunk preparation launch")) return e;
     }
@@ -421,13 +421,13 @@ la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) 
     ws.u = p.u ? base + p.u : nullptr;
     ws.p = base + p.pm;
     ws.qf = base + p.qf;
-    const int32_t chunk_major = la::chunk_major_map(s->n_seqs, s->n_heads, max_chunks) ? 1 : 0;
+    const la::UnitMap map = la::unit_map(s->n_seqs, s->n_heads, s->ckpt_interval, cps, max_chunks, c.cu_host[s->n_seqs]);
     trace_mark(0, c.stream);
     (void)hipGetLastError();
     if (max_chunks > 0) {
-        la::PrepArgs pa{c.q, c.k, c.v, c.g, c.beta, c.cu_dev, s->n_seqs, s->n_heads, s->ckpt_interval, cps,
-                        s->variant, (int32_t)max_chunks, ws, chunk_major};
-        const int64_t blocks = la::chunk_grid_blocks(s->n_seqs, s->n_heads, max_chunks);
+        la::PrepArgs pa{c.q, c.k, c.v, c.g, c.beta, c.cu_dev, s->n_heads, s->ckpt_interval, cps,
+                        s->variant, ws, map};
+        const int64_t blocks = la::unit_map_blocks(map);
         hipLaunchKernelGGL((la::gdr_prep_kernel<T, DK, DV>), dim3((unsigned)blocks), dim3(256), 0, c.stream, pa);
         if (la_status e = hip_check("chunk preparation launch")) return e;
     }
@@ -447,9 +447,8 @@ la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) 
                            c.stream, sa);
         if (la_status e = hip_check("inter-chunk scan launch")) return e;
         if (max_chunks > 0) {
-            la::OutArgs oa{c.o, c.cu_dev, s->n_seqs, s->n_heads, s->ckpt_interval, cps, (int32_t)max_chunks, s->scale,
-                           ws, chunk_major};
-            const int64_t ob = la::chunk_grid_blocks(s->n_seqs, s->n_heads, max_chunks);
+            la::OutArgs oa{c.o, c.cu_dev, s->n_heads, s->ckpt_interval, cps, s->scale, ws, map};
+            const int64_t ob = la::unit_map_blocks(map);
             hipLaunchKernelGGL((la::gdr_out_kernel<T, DK, DV>), dim3((unsigned)ob), dim3(4 * DV), 0, c.stream, oa);
             if (la_status e = hip_check("output launch")) return e;
         }
