@@ -30,10 +30,12 @@ constexpr float kLog2eOut = 1.4426950408889634f;
 //   q[mt][f] = Q[16 mt + c][perm_row(f, g)]      (B operand of Q^T, dk permuted)
 //   p[mt][f] = P[16 mt + c][perm_row(f, g)]      (B operand of P^T, chunk rows permuted)
 //   eg[mt]   = exp(G_{16 mt + c})
-template <typename T, int DK> struct OutFrag {
+// NMT: 16-row tiles of a chunk that can hold tokens; the fragments of P end at
+// the diagonal (vector v <= mt).
+template <typename T, int DK, int NMT> struct OutFrag {
     static constexpr int FS = DK / 4, FU = kChunk / 4;
-    T q[4][FS];
-    T p[4][FU];
+    T q[NMT][FS];
+    T p[NMT][FU];
     float eg[4];
 };
 
@@ -57,23 +59,23 @@ template <typename T> __device__ inline uint32_t head_rows_bytes(int n, int H, i
 
 // Issues the loads of one chunk's read-out operands: the Q and P fragments
 // and the gates of workspace slot-head sh.
-template <typename T, int DK>
-__device__ inline void load_out_frag(OutFrag<T, DK> &f, const Workspace &ws, int64_t sh) {
-    constexpr int VEC = Vec<T>::N, VS = OutFrag<T, DK>::FS / VEC, VU = OutFrag<T, DK>::FU / VEC;
+template <typename T, int DK, int NMT>
+__device__ inline void load_out_frag(OutFrag<T, DK, NMT> &f, const Workspace &ws, int64_t sh) {
+    constexpr int VEC = Vec<T>::N, VS = OutFrag<T, DK, NMT>::FS / VEC, VU = OutFrag<T, DK, NMT>::FU / VEC;
     const int lane = threadIdx.x & 63, c16 = lane & 15;
     constexpr size_t QE = (size_t)kChunk * DK;       // Q elements per slot-head
     const auto rq = make_rsrc((const T *)ws.qf + sh * QE, QE * sizeof(T));
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
         for (int v = 0; v < VS; ++v)
             *(uint4 *)&f.q[mt][v * VEC] = buf_load16(rq, 16u * (uint32_t)lane + 1024u * (mt * VS + v), 0u);
     constexpr size_t PE = (size_t)kChunk * kChunk;   // P elements per slot-head
     const auto rp = make_rsrc((const T *)ws.p + sh * PE, PE * sizeof(T));
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
-        for (int v = 0; v < VU; ++v)
+        for (int v = 0; v < (mt + 1) * VU / 4; ++v)
             *(uint4 *)&f.p[mt][v * VEC] = buf_load16(rp, 16u * (uint32_t)lane + 1024u * (mt * VU + v), 0u);
     // the gates of rows c, 16 + c, 32 + c, 48 + c sit together (G layout)
     const uint4 e = buf_load16(make_rsrc(ws.g + sh * kChunk, kChunk * sizeof(float)), 16u * (uint32_t)c16, 0u);
@@ -86,22 +88,22 @@ __device__ inline void load_out_frag(OutFrag<T, DK> &f, const Workspace &ws, int
 // O^T for one 16-column tile of the state: sb and ub are the scan's operand
 // forms of S_0 (B-operand order of S_0, i.e. A-operand order of S_0^T) and
 // of U; o is the output of head h at chunk row 0, rows n and later masked.
-template <typename T, int DK>
-__device__ inline void out_tile(const OutFrag<T, DK> &f, const T *sb, const T *ub, float scale, T *o, int n,
+template <typename T, int DK, int NMT>
+__device__ inline void out_tile(const OutFrag<T, DK, NMT> &f, const T *sb, const T *ub, float scale, T *o, int n,
                                 int H, int DV, int tile) {
     using M = MT<T>;
-    constexpr int KW = M::KW, FS = OutFrag<T, DK>::FS, FU = OutFrag<T, DK>::FU;
+    constexpr int KW = M::KW, FS = OutFrag<T, DK, NMT>::FS, FU = OutFrag<T, DK, NMT>::FU;
     const int lane = threadIdx.x & 63, g16 = lane >> 4, c16 = lane & 15;
     const auto ro = make_rsrc(o, head_rows_bytes<T>(n, H, DV));
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < NMT; ++mt) {
         f32x4 acc = zero4();
 #pragma unroll
         for (int ks = 0; ks < FS / KW; ++ks) acc = M::mma(M::pack(&sb[ks * KW]), M::pack(&f.q[mt][ks * KW]), acc);
         const float eg = __builtin_amdgcn_exp2f(f.eg[mt] * kLog2eOut);
         acc = acc * eg;
 #pragma unroll
-        for (int ks = 0; ks < FU / KW; ++ks) acc = M::mma(M::pack(&ub[ks * KW]), M::pack(&f.p[mt][ks * KW]), acc);
+        for (int ks = 0; ks < (mt + 1) * FU / 4 / KW; ++ks) acc = M::mma(M::pack(&ub[ks * KW]), M::pack(&f.p[mt][ks * KW]), acc);
         T out[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) out[i] = from_f32<T>(acc[i] * scale);
@@ -125,11 +127,11 @@ struct OutArgs {
 // on its own): one workgroup per (chunk, head, sequence), one wave per
 // column tile, reading the state entering the chunk and U from the
 // workspace.
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, int NMT>
 __global__ __launch_bounds__(4 * DV) void gdr_out_kernel(OutArgs a) {
     using L = WsLayout<T, DK, DV>;
     constexpr int VEC = Vec<T>::N, FS = DK / 4, FU = kChunk / 4;
-    constexpr int VS = FS / VEC, VU = FU / VEC;
+    constexpr int VS = FS / VEC, VU = FU / VEC, VUN = VU * NMT / 4;
     const int lane = threadIdx.x & 63, tile = threadIdx.x >> 6;
     int64_t j;
     int seq, h;
@@ -150,10 +152,10 @@ __global__ __launch_bounds__(4 * DV) void gdr_out_kernel(OutArgs a) {
 #pragma unroll
     for (int v = 0; v < VS; ++v) *(uint4 *)&sb[v * VEC] = buf_load16(rs, 16u * lane, 1024u * (tile * VS + v));
 #pragma unroll
-    for (int v = 0; v < VU; ++v) *(uint4 *)&ub[v * VEC] = buf_load16(ru, 16u * lane, 1024u * (tile * VU + v));
-    OutFrag<T, DK> f;
-    load_out_frag<T, DK>(f, a.ws, sh);
-    out_tile<T, DK>(f, sb, ub, a.scale, (T *)a.o + (t0 * H + h) * DV, n, H, DV, tile);
+    for (int v = 0; v < VUN; ++v) *(uint4 *)&ub[v * VEC] = buf_load16(ru, 16u * lane, 1024u * (tile * VU + v));
+    OutFrag<T, DK, NMT> f;
+    load_out_frag<T, DK, NMT>(f, a.ws, sh);
+    out_tile<T, DK, NMT>(f, sb, ub, a.scale, (T *)a.o + (t0 * H + h) * DV, n, H, DV, tile);
 }
 
 }  // namespace la

@@ -21,8 +21,8 @@
 // inside the chunk; the prediction of row r sees S_0 decayed by exp(Gp_r)
 // plus the rank-one writes of earlier rows decayed by exp(Gp_r - G_s).)
 //
-// K and V are staged row-major only; operands that contract over chunk rows
-// are read with the LDS transpose read (bf16) or one element per lane (fp32).
+// K is staged row-major only; operands that contract over chunk rows are read
+// one element per lane.
 // Exponentials of gate differences use exp2 on log2(e)-scaled cumulative
 // gates; every exponent is a difference formed before exponentiation.
 #pragma once
@@ -78,13 +78,13 @@ __device__ inline void subst_all(float (&x)[4], const float (&L)[16]) {
     }
 }
 
-template <typename T, int DK, int DV> struct alignas(16) PrepSmem {
-    static constexpr int PK = Vec<T>::N;       // row pads keep 16-byte alignment
-    static constexpr int DM = DK > DV ? DK : DV;
-    T ks[kChunk][DK + PK];                     // K, row-major
-    T vs[kChunk][DM + PK];                     // V, row-major
-    float am[kChunk][kChunk + 4];              // A (strictly lower)
-    float xm[kChunk][kChunk + 4];              // X = (I + A)^{-1}
+// NMT: 16-row tiles of a chunk that can hold tokens (chunks have at most
+// min(C, 64) rows; the rows past them are inert and are left out).
+template <int DK, int NMT> struct alignas(16) PrepSmem {
+    static constexpr int R = 16 * NMT;
+    float ks[R][DK + 4];                       // K, row-major (the pad keeps 16-byte alignment)
+    float am[R][kChunk + 4];                   // A (strictly lower)
+    float xm[R][kChunk + 4];                   // X = (I + A)^{-1}
     float ysc[4][16][17];                      // per-wave 16x16 scratch
     float G2[kChunk], Gp2[kChunk], bs[kChunk]; // log2e-scaled gates, beta
     float dW[kChunk], dK[kChunk];              // beta exp(Gp), exp(G_63 - G)
@@ -101,7 +101,7 @@ __device__ inline f32x4 mm16_f32(const float *A, int lda, const float *B, int ld
     return c;
 }
 
-// Operands that contract over the rows of a row-major LDS tile.
+// Transposed reads of a row-major LDS tile.
 template <typename T> struct RowTile;
 
 template <> struct RowTile<__bf16> {
@@ -115,48 +115,28 @@ template <> struct RowTile<__bf16> {
         const __bf16 *p = tile + row * ld + n0 + 4 * (s & 3);
         return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)p);
     }
-    // B operand (32 x 16, natural k order): rows [k0, k0 + 32), columns [n0, n0 + 16)
-    __device__ static inline bf16x8 bfrag(const __bf16 *tile, int ld, int k0, int n0, int lane) {
-        const int g = lane >> 4, s = lane & 15;
-        const i16x4 lo = tr4(tile, ld, k0 + 8 * g + (s >> 2), n0, lane);
-        const i16x4 hi = tr4(tile, ld, k0 + 8 * g + 4 + (s >> 2), n0, lane);
-        typedef short i16x8 __attribute__((ext_vector_type(8)));
-        const i16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        return __builtin_bit_cast(bf16x8, both);
-    }
-    // tile[perm_row(f, g)][n0 + lane % 16] for f = 4q .. 4q + 3
-    __device__ static inline void col4(const __bf16 *tile, int ld, int q, int n0, int lane, float *out) {
-        const int g = lane >> 4, s = lane & 15;
-        const i16x4 v = tr4(tile, ld, 16 * q + 4 * g + (s >> 2), n0, lane);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) out[t] = (float)__builtin_bit_cast(__bf16, (short)v[t]);
-    }
 };
 
-template <> struct RowTile<float> {
-    // B operand (4 x 16): one element per lane
-    __device__ static inline float bfrag(const float *tile, int ld, int k0, int n0, int lane) {
-        return tile[(k0 + (lane >> 4)) * ld + n0 + (lane & 15)];
-    }
-    __device__ static inline void col4(const float *tile, int ld, int q, int n0, int lane, float *out) {
-        const int g = lane >> 4;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) out[t] = tile[(16 * q + 4 * g + t) * ld + n0 + (lane & 15)];
-    }
-};
-
-// Two workgroups per CU where the LDS allows (fp32 operands with a
-// 128-wide head dimension need more than half of it).
-template <typename T, int DK, int DV>
-__global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 : 1) void gdr_prep_kernel(PrepArgs a) {
+// fp32 MFMA issues one 16x16x4 product per 32 cycles, so what bounds a unit is
+// its count of products and the LDS reads that feed them.  Wave w computes row
+// tile w of A and row tile NMT - 1 - w of P (16-byte reads of K's rows, in the
+// order the state's accumulators contract dk) and, of W^T, U~ and K~^T, the column
+// tiles w, w + 4, ... of every row tile: X's fragments are then read once, V
+// goes from memory straight to the lanes that use it, and the products over X's
+// zero triangle are left out.  Without V the LDS holds two workgroups per CU
+// (74 KB at dk = 128).  Three prompts of 1,791, 640 and 257 tokens (8 heads,
+// dk = dv = 128): 24.7 us against 36.9 with V staged and a row tile per wave
+// throughout; 256 tokens with C = 16 (1 head, dk = dv = 64): 3.8 against 11.6 us.
+template <int DK, int DV, int NMT> __global__ __launch_bounds__(256, 2) void gdr_prep_kernel(PrepArgs a) {
+    typedef float T;
     using M = MT<T>;
-    using RT = RowTile<T>;
-    using Sm = PrepSmem<T, DK, DV>;
-    constexpr int KW = M::KW, KSTEP = M::KSTEP, VEC = Vec<T>::N;
-    constexpr int LDK = DK + Sm::PK, LDV = Sm::DM + Sm::PK, LDA = kChunk + 4;
+    using Sm = PrepSmem<DK, NMT>;
+    constexpr int VEC = 4, R = Sm::R, LDA = kChunk + 4;
+    constexpr int NW = DK / 64, NV = DV / 64;   // column tiles of W^T (K~^T) and of U~ per wave
     __shared__ Sm sm;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g16 = lane >> 4, c16 = lane & 15;
     int64_t j;
     int seq, h;
@@ -174,42 +154,32 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
     const T *kin = (const T *)a.k;
     const T *vin = (const T *)a.v;
 
-    // This lane's queries: token row 16 wave + lane % 16 at dk perm_row(f, g)
+    // ---- 1. every global load first; rows past the chunk's end read the last
+    // valid row and are zeroed afterwards.
+    // This lane's queries: token row 16 mp + lane % 16 at dk perm_row(f, g)
     // for f < DK/4 (g = lane / 16), runs of 4.  That is exactly this lane's
-    // part of the B operand of Q^T for token tile `wave` in the order the
+    // part of the B operand of Q^T for token tile mp in the order the
     // state's accumulator layout contracts dk, so it is stored as is for the
     // output, and the P product below contracts dk in the same order.
+    const int mp = NMT - 1 - wave;              // this wave's row tile of P
     T qf[DK / 4];
-    {
-        const int r = 16 * wave + c16, rr = r < n ? r : n - 1;
+    if (mp >= 0) {
+        const int r = 16 * mp + c16, rr = r < n ? r : n - 1;
         const T *qrow = (const T *)a.q + ((t0 + rr) * H + h) * DK + 4 * g16;
 #pragma unroll
-        for (int p4 = 0; p4 < DK / 16; ++p4) {
-            if constexpr (sizeof(T) == 2)
-                *(uint2 *)&qf[4 * p4] = *(const uint2 *)(qrow + 16 * p4);
-            else
-                *(uint4 *)&qf[4 * p4] = *(const uint4 *)(qrow + 16 * p4);
-        }
+        for (int p4 = 0; p4 < DK / 16; ++p4) *(uint4 *)&qf[4 * p4] = *(const uint4 *)(qrow + 16 * p4);
     }
-
-    // ---- 1. stage K, V (row-major), g, beta; clear X ------------------------
-    // Every global load is issued before the first use; rows past the
-    // chunk's end read the last valid row and are zeroed afterwards.
+    // V as the B operand of U~: rows 4 ks + g, one column per lane
+    T vb[NV][4 * NMT];
     {
-        constexpr int KIT = kChunk * DK / VEC / 256, VIT = kChunk * DV / VEC / 256;
-        static_assert(KIT * 256 * VEC == kChunk * DK && VIT * 256 * VEC == kChunk * DV, "tiling");
-        uint4 kr[KIT], vr[VIT];
+        constexpr int KIT = R * DK / VEC / 256;
+        static_assert(KIT * 256 * VEC == R * DK, "tiling");
+        uint4 kr[KIT];
 #pragma unroll
         for (int it = 0; it < KIT; ++it) {
             const int vi = tid + 256 * it, r = vi / (DK / VEC), c = (vi % (DK / VEC)) * VEC;
             const int rr = r < n ? r : n - 1;
             kr[it] = *(const uint4 *)(kin + ((t0 + rr) * H + h) * DK + c);
-        }
-#pragma unroll
-        for (int it = 0; it < VIT; ++it) {
-            const int vi = tid + 256 * it, r = vi / (DV / VEC), c = (vi % (DV / VEC)) * VEC;
-            const int rr = r < n ? r : n - 1;
-            vr[it] = *(const uint4 *)(vin + ((t0 + rr) * H + h) * DV + c);
         }
         float gv = 0.f, bv = 0.f;
         if (tid < kChunk) {
@@ -217,18 +187,19 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
             gv = a.g[(t0 + rr) * H + h];
             bv = a.beta[(t0 + rr) * H + h];
         }
-        for (int e = tid; e < kChunk * LDA; e += 256) (&sm.xm[0][0])[e] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4 * NMT; ++ks) {
+                const int r = 4 * ks + g16, rr = r < n ? r : n - 1;
+                vb[i][ks] = vin[((t0 + rr) * H + h) * DV + 16 * (wave + 4 * i) + c16];
+            }
+        for (int e = tid; e < R * LDA; e += 256) (&sm.xm[0][0])[e] = 0.f;
 #pragma unroll
         for (int it = 0; it < KIT; ++it) {
             const int vi = tid + 256 * it, r = vi / (DK / VEC), c = (vi % (DK / VEC)) * VEC;
             if (r >= n) kr[it] = make_uint4(0, 0, 0, 0);
             *(uint4 *)&sm.ks[r][c] = kr[it];
-        }
-#pragma unroll
-        for (int it = 0; it < VIT; ++it) {
-            const int vi = tid + 256 * it, r = vi / (DV / VEC), c = (vi % (DV / VEC)) * VEC;
-            if (r >= n) vr[it] = make_uint4(0, 0, 0, 0);
-            *(uint4 *)&sm.vs[r][c] = vr[it];
         }
         // ---- 2. chunk-local gate prefix sum (wave 0) --------------------------
         if (wave == 0) {
@@ -244,42 +215,72 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
             sm.dK[lane] = __builtin_amdgcn_exp2f((g63 - x) * kLog2e);
             a.ws.g[sh * kChunk + 4 * (lane & 15) + (lane >> 4)] = x;   // G layout: row 16 m + c at 4 c + m
         }
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4 * NMT; ++ks)
+                if (4 * ks + g16 >= n) vb[i][ks] = 0.f;
     }
     __syncthreads();
 
-    // ---- 3. A = strictly-lower beta_r exp(Gp_r - G_s) K K^T ------------------
-    // Wave w computes row tile w against all four column tiles: four
-    // independent MFMA chains with no branch between them (the tiles above
-    // the diagonal are computed and dropped: they are never read).  The row
-    // tile's K fragments are read once and reused for every column tile.
-    {
+    // ---- 3. A = strictly-lower beta_r exp(Gp_r - G_s) K K^T, row tile `wave`, and
+    // P = (Q K^T) exp(G_r - G_s) on s <= r, row tile mp: a row tile has as many
+    // tiles as its number + 1, so every wave computes NMT + 1 of them.  P is
+    // computed as the tiles K Q^T: the result tile (s tile nt, token tile mp) holds
+    // P[16 mp + c16][16 nt + 4 g + i] in lane (g, c16), which is element 4 nt + i of
+    // that lane's P^T operand, so it is stored straight from the accumulator.
+    // Tiles above the diagonal are neither written nor read.
+    if (wave < NMT) {
         const int mt = wave;
-        typename M::frag ka[DK / KSTEP];
+        auto row = [&](int t, T (&f)[DK / 4]) {
 #pragma unroll
-        for (int ks = 0; ks < DK / KSTEP; ++ks) ka[ks] = M::pack(&sm.ks[16 * mt + c16][ks * KSTEP + g16 * KW]);
-        f32x4 acc[4];
+            for (int p4 = 0; p4 < DK / 16; ++p4)
+                *(uint4 *)&f[4 * p4] = *(const uint4 *)&sm.ks[16 * t + c16][16 * p4 + 4 * g16];
+        };
+        T kb[DK / 4];
+        {
+            T ka[DK / 4];
+            row(mt, ka);
+            const float4 brow = *(const float4 *)&sm.bs[16 * mt + 4 * g16];
+            const float4 gprow = *(const float4 *)&sm.Gp2[16 * mt + 4 * g16];
+            const float bv[4] = {brow.x, brow.y, brow.z, brow.w};
+            const float gv[4] = {gprow.x, gprow.y, gprow.z, gprow.w};
+            for (int nt = 0; nt <= mt; ++nt) {   // wave-uniform
+                row(nt, kb);
+                f32x4 acc = zero4();
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            acc[nt] = zero4();
+                for (int f = 0; f < DK / 4; ++f) acc = M::mma(ka[f], kb[f], acc);
+                const float gcol = sm.G2[16 * nt + c16];
 #pragma unroll
-            for (int ks = 0; ks < DK / KSTEP; ++ks)
-                acc[nt] = M::mma(ka[ks], M::pack(&sm.ks[16 * nt + c16][ks * KSTEP + g16 * KW]), acc[nt]);
-        }
-        const float4 brow = *(const float4 *)&sm.bs[16 * mt + 4 * g16];
-        const float4 gprow = *(const float4 *)&sm.Gp2[16 * mt + 4 * g16];
-        const float bv[4] = {brow.x, brow.y, brow.z, brow.w};
-        const float gv[4] = {gprow.x, gprow.y, gprow.z, gprow.w};
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            if (nt > mt) continue;   // wave-uniform
-            const float gcol = sm.G2[16 * nt + c16];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = 16 * mt + 4 * g16 + i, s = 16 * nt + c16;
-                const float e = __builtin_amdgcn_exp2f(gv[i] - gcol);
-                sm.am[r][s] = (s < r) ? bv[i] * e * acc[nt][i] : 0.f;
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 16 * mt + 4 * g16 + i, s = 16 * nt + c16;
+                    const float e = __builtin_amdgcn_exp2f(gv[i] - gcol);
+                    sm.am[r][s] = (s < r) ? bv[i] * e * acc[i] : 0.f;
+                }
             }
         }
+        const float gr = sm.G2[16 * mp + c16];
+        T *pout = (T *)a.ws.p + sh * WsLayout<T, DK, DV>::p_elems;
+        for (int nt = 0; nt <= mp; ++nt) {
+            row(nt, kb);
+            f32x4 pc = zero4();
+#pragma unroll
+            for (int f = 0; f < DK / 4; ++f) pc = M::mma(kb[f], qf[f], pc);
+            const float4 gs = *(const float4 *)&sm.G2[16 * nt + 4 * g16];
+            const float gsv[4] = {gs.x, gs.y, gs.z, gs.w};
+            T vals[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool in = 16 * nt + 4 * g16 + i <= 16 * mp + c16;
+                vals[i] = in ? pc[i] * __builtin_amdgcn_exp2f(gr - gsv[i]) : 0.f;
+            }
+            *(uint4 *)(pout + ((size_t)(mp * 4 + nt) * 64 + lane) * VEC) = *(const uint4 *)vals;
+        }
+        constexpr int NQ = DK / 4 / VEC;
+        T *qout = (T *)a.ws.qf + sh * WsLayout<T, DK, DV>::qf_elems;
+#pragma unroll
+        for (int v = 0; v < NQ; ++v)
+            *(uint4 *)(qout + ((size_t)(mp * NQ + v) * 64 + lane) * VEC) = *(const uint4 *)&qf[v * VEC];
     }
     __syncthreads();
 
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
     // r = lane % 16, holds row r of columns 4q .. 4q + 3 of the block's
     // inverse.  Each x[r] receives the updates L[r][s] x[s] in the order
     // s = 0, 1, ..., as forward substitution does.
-    {
+    if (wave < NMT) {
         const int base = 16 * wave, q = lane >> 4, r = lane & 15;
         float L[16];
 #pragma unroll
@@ -307,9 +308,9 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
     }
     __syncthreads();
     // off-diagonal blocks by bands: X_ij = -X_ii sum_{k=j}^{i-1} A_ik X_kj
-    for (int d = 1; d < 4; ++d) {
+    for (int d = 1; d < NMT; ++d) {
         const int bi = d + wave, bj = wave;
-        const bool active = bi < 4;
+        const bool active = bi < NMT;
         if (active) {
             f32x4 y = zero4();
             for (int bk = bj; bk < bi; ++bk)
@@ -330,119 +331,69 @@ __global__ __launch_bounds__(256, sizeof(PrepSmem<T, DK, DV>) <= 80 * 1024 ? 2 :
         __syncthreads();
     }
 
-    // ---- 5. W, U~ = X diag(beta) V, K~^T, P and Q fragments --------------------
+    // ---- 5. W, U~ = X diag(beta) V and the K~^T fragments, column tiles wave,
+    // wave + 4, ...: X's fragments of every row tile (k-steps up to its diagonal)
     {
-        const int mt = wave;
-        constexpr int NKS = kChunk / KSTEP;
-        typename M::frag f1[NKS], f2[NKS];
+        T x1[NMT][4 * NMT], x2[NMT][4 * NMT];   // X diag(beta exp(Gp)), X diag(beta)
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            T v1[KW], v2[KW];
+        for (int ks = 0; ks < 4 * NMT; ++ks) {
+            const int s = 4 * ks + g16;
+            const float w1 = sm.dW[s], w2 = sm.bs[s];
 #pragma unroll
-            for (int jj = 0; jj < KW; ++jj) {
-                const int s = ks * KSTEP + g16 * KW + jj;
-                const float x = sm.xm[16 * mt + c16][s];
-                v1[jj] = from_f32<T>(x * sm.dW[s]);
-                v2[jj] = from_f32<T>(x * sm.bs[s]);
-            }
-            f1[ks] = M::pack(v1);
-            f2[ks] = M::pack(v2);
+            for (int mt = 0; mt < NMT; ++mt)
+                if (ks < 4 * (mt + 1)) {
+                    const float x = sm.xm[16 * mt + c16][s];
+                    x1[mt][ks] = x * w1;
+                    x2[mt][ks] = x * w2;
+                }
         }
         // W^T tile (dk tile nt, row tile mt) = K^T (X diag(dW))^T: per lane the
-        // K fragment read as a B operand of K is the A operand of K^T, and f1
+        // element of K read as a B operand of K is the A operand of K^T, and x1
         // (A operand of X diag(dW)) is the B operand of its transpose.  The
         // accumulator then holds W[16 mt + c16][16 nt + 4 g + i], element
         // 4 nt + i of this lane's -W fragment in the scan's permuted dk
         // order, so -W is stored straight from registers.
-        {
-            T wf[DK / 4];
+        T *wout = (T *)a.ws.w + sh * WsLayout<T, DK, DV>::w_elems;
+        T *kout = (T *)a.ws.kt + sh * WsLayout<T, DK, DV>::kt_elems;
 #pragma unroll
-            for (int nt = 0; nt < DK / 16; ++nt) {
-                f32x4 acc = zero4();
+        for (int i = 0; i < NW; ++i) {
+            const int nt = wave + 4 * i;
+            T kf[4 * NMT];
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks)
-                    acc = M::mma(RT::bfrag(&sm.ks[0][0], LDK, ks * KSTEP, 16 * nt, lane), f1[ks], acc);
+            for (int ks = 0; ks < 4 * NMT; ++ks) kf[ks] = sm.ks[4 * ks + g16][16 * nt + c16];
+            f32x4 acc[NMT];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) wf[4 * nt + i] = from_f32<T>(-acc[i]);
+            for (int ks = 0; ks < 4 * NMT; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt)
+                    if (ks < 4 * (mt + 1)) acc[mt] = M::mma(kf[ks], x1[mt][ks], ks == 0 ? zero4() : acc[mt]);
+#pragma unroll
+            for (int mt = 0; mt < NMT; ++mt)
+                *(float4 *)(wout + ((size_t)(mt * (DK / 16) + nt) * 64 + lane) * VEC) =
+                    make_float4(-acc[mt][0], -acc[mt][1], -acc[mt][2], -acc[mt][3]);
+            // K~^T: the lane holds chunk rows perm_row(f, g) of dk row 16 nt + c16
+#pragma unroll
+            for (int q = 0; q < NMT; ++q) {
+                const float4 d = *(const float4 *)&sm.dK[16 * q + 4 * g16];
+                const int r = 16 * q + 4 * g16, c = 16 * nt + c16;
+                *(float4 *)(kout + ((size_t)(nt * 4 + q) * 64 + lane) * VEC) =
+                    make_float4(sm.ks[r][c] * d.x, sm.ks[r + 1][c] * d.y, sm.ks[r + 2][c] * d.z, sm.ks[r + 3][c] * d.w);
             }
-            constexpr int NV = DK / 4 / VEC;
-            T *wout = (T *)a.ws.w + sh * WsLayout<T, DK, DV>::w_elems;
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                *(uint4 *)(wout + ((size_t)(mt * NV + v) * 64 + lane) * VEC) = *(const uint4 *)&wf[v * VEC];
         }
         T *ut = (T *)a.ws.ut + sh * WsLayout<T, DK, DV>::ut_elems;
 #pragma unroll
-        for (int nt = 0; nt < DV / 16; ++nt) {
-            f32x4 acc = zero4();
+        for (int i = 0; i < NV; ++i) {
+            const int nt = wave + 4 * i;
+            f32x4 acc[NMT];
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-                acc = M::mma(f2[ks], RT::bfrag(&sm.vs[0][0], LDV, ks * KSTEP, 16 * nt, lane), acc);
-            T u4[4];
+            for (int ks = 0; ks < 4 * NMT; ++ks)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) u4[i] = from_f32<T>(acc[i]);
-            if constexpr (sizeof(T) == 4)
-                *(uint4 *)(ut + ((size_t)(nt * 4 + mt) * 64 + lane) * 4) = *(const uint4 *)u4;
-            else
-                *(uint2 *)(ut + ((size_t)(nt * 4 + mt) * 64 + lane) * 4) = *(const uint2 *)u4;
-        }
-        // K~^T: per dk row tile, lane holds 16 values at chunk rows perm_row(f, g)
-        T *kout = (T *)a.ws.kt + sh * WsLayout<T, DK, DV>::kt_elems;
-        constexpr int NV2 = 16 / VEC;
-        for (int kt = wave; kt < DK / 16; kt += 4) {
-            T vals[16];
+                for (int mt = 0; mt < NMT; ++mt)
+                    if (ks < 4 * (mt + 1)) acc[mt] = M::mma(x2[mt][ks], vb[i][ks], ks == 0 ? zero4() : acc[mt]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float c4[4];
-                RT::col4(&sm.ks[0][0], LDK, q, 16 * kt, lane, c4);
-                const float4 d = *(const float4 *)&sm.dK[16 * q + 4 * g16];
-                vals[4 * q + 0] = from_f32<T>(c4[0] * d.x);
-                vals[4 * q + 1] = from_f32<T>(c4[1] * d.y);
-                vals[4 * q + 2] = from_f32<T>(c4[2] * d.z);
-                vals[4 * q + 3] = from_f32<T>(c4[3] * d.w);
-            }
-#pragma unroll
-            for (int v = 0; v < NV2; ++v)
-                *(uint4 *)(kout + ((size_t)(kt * NV2 + v) * 64 + lane) * VEC) = *(const uint4 *)&vals[v * VEC];
-        }
-        // P for token tile mt, computed as the tiles K Q^T: the result tile
-        // (s tile nt, token tile mt) holds P[16 mt + c16][16 nt + 4 g + i] in
-        // lane (g, c16), which is element 4 nt + i of that lane's P^T
-        // operand, so the fragments are stored straight from the
-        // accumulators.  Tiles above the diagonal are zero.
-        {
-            const float gr = sm.G2[16 * mt + c16];
-            T vals[16];
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                f32x4 acc = zero4();
-                if (nt <= mt) {
-#pragma unroll
-                    for (int ks = 0; ks < DK / KSTEP; ++ks) {
-                        const int f0 = ks * KW;
-                        const T *krow = &sm.ks[16 * nt + c16][0];
-                        acc = M::mma(M::pack2(krow + perm_row(f0, g16), krow + perm_row(f0 + (KW > 4 ? 4 : 0), g16)),
-                                     M::pack(&qf[f0]), acc);
-                    }
-                }
-                const float4 gs = *(const float4 *)&sm.G2[16 * nt + 4 * g16];
-                const float gsv[4] = {gs.x, gs.y, gs.z, gs.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int s = 16 * nt + 4 * g16 + i, r = 16 * mt + c16;
-                    const float e = __builtin_amdgcn_exp2f(gr - gsv[i]);
-                    vals[4 * nt + i] = from_f32<T>(s <= r ? acc[i] * e : 0.f);
-                }
-            }
-            T *pout = (T *)a.ws.p + sh * WsLayout<T, DK, DV>::p_elems;
-#pragma unroll
-            for (int v = 0; v < NV2; ++v)
-                *(uint4 *)(pout + ((size_t)(mt * NV2 + v) * 64 + lane) * VEC) = *(const uint4 *)&vals[v * VEC];
-            constexpr int NQ = DK / 4 / VEC;
-            T *qout = (T *)a.ws.qf + sh * WsLayout<T, DK, DV>::qf_elems;
-#pragma unroll
-            for (int v = 0; v < NQ; ++v)
-                *(uint4 *)(qout + ((size_t)(mt * NQ + v) * 64 + lane) * VEC) = *(const uint4 *)&qf[v * VEC];
+            for (int mt = 0; mt < NMT; ++mt)
+                *(float4 *)(ut + ((size_t)(nt * 4 + mt) * 64 + lane) * 4) =
+                    make_float4(acc[mt][0], acc[mt][1], acc[mt][2], acc[mt][3]);
         }
     }
 }

@@ -261,7 +261,8 @@ template <int DK> struct ScanGeom {
     static constexpr int MTW = 4 / NW;      // U row tiles each wave reduces
 };
 
-template <typename T, int DK, int DV>
+// NMT: 16-row tiles of a chunk that can hold tokens (the rows past them are inert).
+template <typename T, int DK, int DV, int NMT>
 __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
     using M = MT<T>;
     using L = WsLayout<T, DK, DV>;
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
     constexpr int FU = kChunk / 4;          // per-lane operand values over chunk rows
     constexpr int FW = 8;                   // per-lane values of one wave's 32-row dk slice
     constexpr int VW = FW / VEC;            // 16-byte vectors per slice
-    constexpr int VU = FU / VEC;
+    constexpr int VU = FU / VEC, VUN = VU * NMT / 4;   // vectors per slice; those of rows with tokens
     static_assert(FW % VEC == 0 && FU % VEC == 0 && NW * 32 == DK, "tiling");
 
     __shared__ f32x4 part[NW][4][64];       // partial products W_w S_w, C-layout
@@ -334,17 +335,18 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
         o.ckid = ck.load_id(jj / a.cps);
         const auto ru = make_rsrc((const T *)a.ws.ut + sh * L::ut_elems, L::ut_elems * sizeof(T));
 #pragma unroll
-        for (int m = 0; m < MTW; ++m) o.ut[m] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + w * MTW + m));
+        for (int m = 0; m < MTW; ++m)
+            if (w * MTW + m < NMT) o.ut[m] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + w * MTW + m));
         const auto rw = make_rsrc((const T *)a.ws.w + sh * L::w_elems, L::w_elems * sizeof(T));
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int v = 0; v < VW; ++v) o.wn[mt][v] = buf_load16(rw, lane16, 1024u * (mt * (FS / VEC) + w * VW + v));
         const auto rk = make_rsrc((const T *)a.ws.kt + sh * L::kt_elems, L::kt_elems * sizeof(T));
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int v = 0; v < VU; ++v) o.kt[t][v] = buf_load16(rk, lane16, 1024u * ((2 * w + t) * VU + v));
+            for (int v = 0; v < VUN; ++v) o.kt[t][v] = buf_load16(rk, lane16, 1024u * ((2 * w + t) * VU + v));
     };
 
     auto step = [&](const Ops &o, int j) {
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
         // partial products over this wave's 32 state rows; the wave that
         // reduces row tile mt starts its partial from U~
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
+        for (int mt = 0; mt < NMT; ++mt) {
             const T *wv = (const T *)&o.wn[mt][0];
             f32x4 acc = zero4();
 #pragma unroll
@@ -378,6 +380,7 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
 #pragma unroll
         for (int m = 0; m < MTW; ++m) {
             const int mt = w * MTW + m;
+            if (mt >= NMT) break;   // wave-uniform
             f32x4 pp[NW];
 #pragma unroll
             for (int p = 0; p < NW; ++p) pp[p] = part[p][mt][lane];
@@ -392,11 +395,11 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
         __syncthreads();
         uint4 ub[VU];
 #pragma unroll
-        for (int v = 0; v < VU; ++v) ub[v] = ubuf[v][lane];
+        for (int v = 0; v < VUN; ++v) ub[v] = ubuf[v][lane];
         {
             const auto rs = make_rsrc((T *)a.ws.u + sh * L::u_elems, L::u_elems * sizeof(T));
 #pragma unroll
-            for (int v = 0; v < VU; ++v)
+            for (int v = 0; v < VUN; ++v)
                 if (v % NW == w) buf_store16(ub[v], rs, lane16, 1024u * (tile * VU + v));
         }
         // S = exp(G_63) S + K~^T U on this wave's rows
@@ -407,7 +410,7 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
             const T *kv = (const T *)&o.kt[t][0];
             f32x4 acc = S[t] * decay;
 #pragma unroll
-            for (int ks = 0; ks < FU / KW; ++ks)
+            for (int ks = 0; ks < FU * NMT / 4 / KW; ++ks)
                 acc = M::mma(M::pack(&kv[ks * KW]), M::pack(&uvals[ks * KW]), acc);
             S[t] = acc;
         }
@@ -449,12 +452,12 @@ __device__ inline void lds_barrier() {
 // state update, with the next chunk's operands in flight while one is
 // computed.  scan1_chunks runs the whole sequence of one (sequence, head) on
 // one tile and writes the checkpoints.  It hands the state entering each
-// chunk and U to the split output kernel through the workspace or, with
-// HANDOFF, to the workgroup's output wave through the LDS slots hs (one
-// barrier per chunk).  HANDOFF is a compile-time choice: a run-time test
-// would split a chunk's step into several basic blocks, and the load/MFMA
-// interleave below is scheduled within one block.
-template <typename T, int DK, int DV, bool HANDOFF>
+// chunk and U to the workgroup's output wave through the LDS slots hs (one
+// barrier per chunk).  NMT: 16-row tiles of a chunk that can hold tokens
+// (chunks have at most min(C, 64) rows); the rows past them are inert, so their
+// operands are neither read nor multiplied.  256 tokens with C = 16 (1 head,
+// dk = dv = 64): 15.2 us against 39.9 over all four row tiles.
+template <typename T, int DK, int DV, int NMT>
 __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile, int len, int64_t base,
                                     int nch, f32x4 (&S)[DK / 16], Handoff<T, DK> *hs) {
     using M = MT<T>;
@@ -463,9 +466,9 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
     constexpr int RT = DK / 16;             // state row tiles
     constexpr int FS = DK / 4;              // per-lane operand values over dk
     constexpr int FU = kChunk / 4;          // per-lane operand values over chunk rows
-    constexpr int VS = FS / VEC, VU = FU / VEC;
-    constexpr int kMfmas = 4 * (FS / KW) + RT * (FU / KW);       // per chunk
-    constexpr int kLoads = 1 + 4 + 4 * VS + RT * VU;              // operand loads per chunk
+    constexpr int VS = FS / VEC, VUN = FU / VEC * NMT / 4;
+    constexpr int kMfmas = NMT * (FS / KW) + RT * (FU * NMT / 4 / KW);       // per chunk
+    constexpr int kLoads = 1 + NMT + NMT * VS + RT * VUN;              // operand loads per chunk
 
     const int lane = threadIdx.x & 63, g16 = lane >> 4, c16 = lane & 15;
     const int H = a.n_heads;
@@ -481,9 +484,9 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
     struct Ops {
         float gl;
         int ckid;             // page id of the checkpoint this chunk would end (paged)
-        f32x4 ut[4];
-        uint4 wn[4][VS];
-        uint4 kt[RT][VU];
+        f32x4 ut[NMT];
+        uint4 wn[NMT][VS];
+        uint4 kt[RT][VUN];
     };
     const uint32_t lane16 = 16u * (uint32_t)lane;
     auto load = [&](Ops &o, int jj) {
@@ -492,35 +495,27 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
         o.ckid = ck.load_id(jj / a.cps);
         const auto ru = make_rsrc((const T *)a.ws.ut + sh * L::ut_elems, L::ut_elems * sizeof(T));
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) o.ut[mt] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + mt));
+        for (int mt = 0; mt < NMT; ++mt) o.ut[mt] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + mt));
         const auto rw = make_rsrc((const T *)a.ws.w + sh * L::w_elems, L::w_elems * sizeof(T));
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int v = 0; v < VS; ++v) o.wn[mt][v] = buf_load16(rw, lane16 + 1024u * (mt * VS + v), 0u);
         const auto rk = make_rsrc((const T *)a.ws.kt + sh * L::kt_elems, L::kt_elems * sizeof(T));
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int v = 0; v < VU; ++v) o.kt[t][v] = buf_load16(rk, lane16 + 1024u * (t * VU + v), 0u);
+            for (int v = 0; v < VUN; ++v) o.kt[t][v] = buf_load16(rk, lane16 + 1024u * (t * (FU / VEC) + v), 0u);
     };
     auto step = [&](const Ops &o, int jj) {
-        const int64_t sh = (base + jj) * H + h;
         T sb[FS];
 #pragma unroll
         for (int f = 0; f < FS; ++f) sb[f] = from_f32<T>(S[f >> 2][f & 3]);
-        if constexpr (HANDOFF) {
 #pragma unroll
-            for (int v = 0; v < VS; ++v) hs->sb[jj & 1][v][lane] = *(const uint4 *)&sb[v * VEC];
-        } else {
-            const auto rs = make_rsrc((T *)a.ws.sc + sh * L::sc_elems, L::sc_elems * sizeof(T));
+        for (int v = 0; v < VS; ++v) hs->sb[jj & 1][v][lane] = *(const uint4 *)&sb[v * VEC];
+        f32x4 U[NMT];
 #pragma unroll
-            for (int v = 0; v < VS; ++v)
-                buf_store16(*(const uint4 *)&sb[v * VEC], rs, lane16, 1024u * (tile * VS + v));
-        }
-        f32x4 U[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
+        for (int mt = 0; mt < NMT; ++mt) {
             const T *wv = (const T *)&o.wn[mt][0];
             f32x4 acc = o.ut[mt];
 #pragma unroll
@@ -528,25 +523,18 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
                 acc = M::mma(M::pack(&wv[ks * KW]), M::pack(&sb[ks * KW]), acc);
             U[mt] = acc;
         }
-        T ub[FU];
+        T ub[FU * NMT / 4];
 #pragma unroll
-        for (int f = 0; f < FU; ++f) ub[f] = from_f32<T>(U[f >> 2][f & 3]);
-        if constexpr (HANDOFF) {
+        for (int f = 0; f < FU * NMT / 4; ++f) ub[f] = from_f32<T>(U[f >> 2][f & 3]);
 #pragma unroll
-            for (int v = 0; v < VU; ++v) hs->ub[jj & 1][v][lane] = *(const uint4 *)&ub[v * VEC];
-        } else {
-            const auto rs = make_rsrc((T *)a.ws.u + sh * L::u_elems, L::u_elems * sizeof(T));
-#pragma unroll
-            for (int v = 0; v < VU; ++v)
-                buf_store16(*(const uint4 *)&ub[v * VEC], rs, lane16, 1024u * (tile * VU + v));
-        }
+        for (int v = 0; v < VUN; ++v) hs->ub[jj & 1][v][lane] = *(const uint4 *)&ub[v * VEC];
         const float decay = expf(o.gl);
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             const T *kv = (const T *)&o.kt[t][0];
             f32x4 acc = S[t] * decay;
 #pragma unroll
-            for (int ks = 0; ks < FU / KW; ++ks)
+            for (int ks = 0; ks < FU * NMT / 4 / KW; ++ks)
                 acc = M::mma(M::pack(&kv[ks * KW]), M::pack(&ub[ks * KW]), acc);
             S[t] = acc;
         }
@@ -564,7 +552,7 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
         if (cur.advance()) {
             if (float *d = ck.next(o.ckid)) store_state_tiles<RT, DV>(d, S, lane_off);
         }
-        if constexpr (HANDOFF) lds_barrier();   // this chunk's slot is written; the output wave may read it
+        lds_barrier();   // this chunk's slot is written; the output wave may read it
     };
     scan_ring<1>(nch, load, step, (Ops *)nullptr);
 }
@@ -575,14 +563,14 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
 // loaded one chunk ahead.  It passes exactly one barrier per chunk, as the
 // scan wave does; reading slot j & 1 before the barrier of chunk j + 1 keeps
 // the scan wave from overwriting it (that write follows that barrier).
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, int NMT>
 __device__ inline void out_wave_chunks(const ScanArgs &a, int h, int tile, int64_t cu0, int len, int64_t base,
                                        int nch, const Handoff<T, DK> *hs) {
-    using F = OutFrag<T, DK>;
-    constexpr int VEC = Vec<T>::N, VS = Handoff<T, DK>::VS, VU = Handoff<T, DK>::VU;
+    using F = OutFrag<T, DK, NMT>;
+    constexpr int VEC = Vec<T>::N, VS = Handoff<T, DK>::VS, VU = Handoff<T, DK>::VU, VUN = VU * NMT / 4;
     const int lane = threadIdx.x & 63, H = a.n_heads;
     ChunkCursor cur{0, a.C, len, a.C};
-    auto load = [&](F &f, int jj) { load_out_frag<T, DK>(f, a.ws, (base + jj) * H + h); };
+    auto load = [&](F &f, int jj) { load_out_frag<T, DK, NMT>(f, a.ws, (base + jj) * H + h); };
     auto step = [&](const F &f, int jj) {
         const int lo = cur.pos;
         cur.advance();
@@ -592,8 +580,8 @@ __device__ inline void out_wave_chunks(const ScanArgs &a, int h, int tile, int64
 #pragma unroll
         for (int v = 0; v < VS; ++v) *(uint4 *)&sb[v * VEC] = hs->sb[jj & 1][v][lane];
 #pragma unroll
-        for (int v = 0; v < VU; ++v) *(uint4 *)&ub[v * VEC] = hs->ub[jj & 1][v][lane];
-        out_tile<T, DK>(f, sb, ub, a.scale, (T *)a.o + ((cu0 + lo) * H + h) * DV, n, H, DV, tile);
+        for (int v = 0; v < VUN; ++v) *(uint4 *)&ub[v * VEC] = hs->ub[jj & 1][v][lane];
+        out_tile<T, DK, NMT>(f, sb, ub, a.scale, (T *)a.o + ((cu0 + lo) * H + h) * DV, n, H, DV, tile);
     };
     scan_ring<1>(nch, load, step, (F *)nullptr);
 }
@@ -613,37 +601,12 @@ __device__ inline void load_state_tile(const float *src, int tile, f32x4 (&S)[DK
     }
 }
 
-// Whole-sequence scan: one wave per (sequence, head, 16-column tile).  The
-// NT waves of one (sequence, head) land on one XCD (workgroups are dealt to
-// the 8 XCDs round-robin) and share the chunk operands through its L2.
-template <typename T, int DK, int DV>
-__global__ __launch_bounds__(64) void gdr_scan1_kernel(ScanArgs a) {
-    constexpr int NT = DV / 16;
-    const int b = blockIdx.x, xcd = b & 7, q = b >> 3;
-    const int pair = chain_of_rank(a, xcd + 8 * (q / NT)), tile = q % NT;
-    const int H = a.n_heads;
-    if (pair < 0) return;
-    const int seq = pair / H, h = pair % H;
-    const int cu0 = a.cu[seq], len = a.cu[seq + 1] - cu0;
-    const int nch = n_chunks32(len, a.C, a.cps);
-    const int64_t base = slot_base_dev(cu0, seq, a.C, a.cps);
-    const size_t state_off = (size_t)pair * DK * DV;
-    f32x4 S[DK / 16];
-    load_state_tile<DK, DV>(start_state(a, seq, h, (size_t)DK * DV, tile == 0), tile, S);
-    scan1_chunks<T, DK, DV, false>(a, seq, h, tile, len, base, nch, S, nullptr);
-    if (a.final_state) {
-        const int lane = threadIdx.x;
-        store_state_tiles<DK / 16, DV>(a.final_state + state_off, S,
-                                       4u * (uint32_t)(4 * (lane >> 4) * DV + 16 * tile + (lane & 15)));
-    }
-}
-
-// Scan with output: the single-wave scan of gdr_scan1_kernel (wave 0) plus
+// Scan with output: the single-wave scan (scan1_chunks, wave 0) plus
 // an output wave (wave 1) per (sequence, head, 16-column tile).  The state
 // entering each chunk and U go from one wave to the other through LDS, so
 // they never reach HBM, and the output product runs on another SIMD beside
 // the scan's chain.
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, int NMT>
 __global__ __launch_bounds__(128) void gdr_scan1o_kernel(ScanArgs a) {
     constexpr int NT = DV / 16;
     __shared__ Handoff<T, DK> hs;
@@ -660,14 +623,14 @@ __global__ __launch_bounds__(128) void gdr_scan1o_kernel(ScanArgs a) {
         const size_t state_off = (size_t)pair * DK * DV;
         f32x4 S[DK / 16];
         load_state_tile<DK, DV>(start_state(a, seq, h, (size_t)DK * DV, tile == 0), tile, S);
-        scan1_chunks<T, DK, DV, true>(a, seq, h, tile, len, base, nch, S, &hs);
+        scan1_chunks<T, DK, DV, NMT>(a, seq, h, tile, len, base, nch, S, &hs);
         if (a.final_state) {
             const int lane = threadIdx.x & 63;
             store_state_tiles<DK / 16, DV>(a.final_state + state_off, S,
                                            4u * (uint32_t)(4 * (lane >> 4) * DV + 16 * tile + (lane & 15)));
         }
     } else {
-        out_wave_chunks<T, DK, DV>(a, h, tile, cu0, len, base, nch, &hs);
+        out_wave_chunks<T, DK, DV, NMT>(a, h, tile, cu0, len, base, nch, &hs);
     }
 }
 

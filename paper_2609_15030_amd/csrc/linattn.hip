@@ -405,9 +405,10 @@ la_status launch_fused(const PrefillCall &c, const WsPlan &p, int64_t max_chunks
 }
 
 // fp32: per-chunk preparation, then the one-tile scan with its output wave
-// (dk = 64), or the dk-split scan and the split output kernel (dk = 128).
-template <int DK, int DV>
-la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) {
+// (dk = 64), or the dk-split scan and the split output kernel (dk = 128), over
+// the NMT 16-row tiles of a chunk that can hold tokens (min(C, 64) rows).
+template <int DK, int DV, int NMT>
+la_status launch_f32_tiles(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) {
     typedef float T;
     const la_shape *s = c.shape;
     const int cps = la::chunks_per_interval(s->ckpt_interval);
@@ -428,7 +429,7 @@ la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) 
         la::PrepArgs pa{c.q, c.k, c.v, c.g, c.beta, c.cu_dev, s->n_heads, s->ckpt_interval, cps,
                         s->variant, ws, map};
         const int64_t blocks = la::unit_map_blocks(map);
-        hipLaunchKernelGGL((la::gdr_prep_kernel<T, DK, DV>), dim3((unsigned)blocks), dim3(256), 0, c.stream, pa);
+        hipLaunchKernelGGL((la::gdr_prep_kernel<DK, DV, NMT>), dim3((unsigned)blocks), dim3(256), 0, c.stream, pa);
         if (la_status e = hip_check("chunk preparation launch")) return e;
     }
     trace_mark(1, c.stream);
@@ -439,22 +440,32 @@ la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) 
     if constexpr (DK != 128) {   // LA_FORM_TILE_SCAN_OUT (the dk = 128 kernels are not built for it)
         // the scan's output wave produces the output: no output launch
         trace_mark(2, c.stream);
-        hipLaunchKernelGGL((la::gdr_scan1o_kernel<T, DK, DV>), dim3((unsigned)blocks), dim3(128), 0, c.stream, sa);
+        hipLaunchKernelGGL((la::gdr_scan1o_kernel<T, DK, DV, NMT>), dim3((unsigned)blocks), dim3(128), 0, c.stream, sa);
         if (la_status e = hip_check("inter-chunk scan launch")) return e;
     } else {
         trace_mark(2, c.stream);
-        hipLaunchKernelGGL((la::gdr_scan_kernel<T, DK, DV>), dim3((unsigned)blocks), dim3(64 * la::ScanGeom<DK>::NW), 0,
+        hipLaunchKernelGGL((la::gdr_scan_kernel<T, DK, DV, NMT>), dim3((unsigned)blocks), dim3(64 * la::ScanGeom<DK>::NW), 0,
                            c.stream, sa);
         if (la_status e = hip_check("inter-chunk scan launch")) return e;
         if (max_chunks > 0) {
             la::OutArgs oa{c.o, c.cu_dev, s->n_heads, s->ckpt_interval, cps, s->scale, ws, map};
             const int64_t ob = la::unit_map_blocks(map);
-            hipLaunchKernelGGL((la::gdr_out_kernel<T, DK, DV>), dim3((unsigned)ob), dim3(4 * DV), 0, c.stream, oa);
+            hipLaunchKernelGGL((la::gdr_out_kernel<T, DK, DV, NMT>), dim3((unsigned)ob), dim3(4 * DV), 0, c.stream, oa);
             if (la_status e = hip_check("output launch")) return e;
         }
     }
     trace_mark(3, c.stream);
     return LA_OK;
+}
+
+template <int DK, int DV>
+la_status launch_f32(const PrefillCall &c, const WsPlan &p, int64_t max_chunks) {
+    switch ((std::min(c.shape->ckpt_interval, la::kChunk) + 15) / 16) {
+        case 1: return launch_f32_tiles<DK, DV, 1>(c, p, max_chunks);
+        case 2: return launch_f32_tiles<DK, DV, 2>(c, p, max_chunks);
+        case 3: return launch_f32_tiles<DK, DV, 3>(c, p, max_chunks);
+        default: return launch_f32_tiles<DK, DV, 4>(c, p, max_chunks);
+    }
 }
 
 template <int DK, int DV>
