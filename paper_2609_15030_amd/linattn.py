@@ -144,12 +144,15 @@ def _dptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
-def _hptr(a, dtype) -> Optional[ctypes.c_void_p]:
-    """Host pointer of a NumPy array (converted to ``dtype``, kept alive by the caller)."""
+def _hptr(a, dtype) -> Optional[int]:
+    """Address of a NumPy array of ``dtype``, kept alive by the caller.  Read
+    from the array interface (1.2 us): a.ctypes.data_as takes 3 us an array,
+    and a resumed paged prefill passes three, which made its smallest
+    calls wait for the host."""
     if a is None:
         return None
     assert a.dtype == dtype and a.flags.c_contiguous
-    return a.ctypes.data_as(ctypes.c_void_p)
+    return a.__array_interface__["data"][0]
 
 
 def _stream(stream) -> Optional[int]:
