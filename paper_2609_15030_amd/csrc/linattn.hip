@@ -260,9 +260,13 @@ la::ScanArgs scan_args(const PrefillCall &c, const la::Workspace &ws) {
 }
 
 // Per-chunk step of one fused-scan workgroup by column width, relative to
-// the 64-column form's (measured on the MI355X at dk = dv = 128, all CUs
-// busy): narrower workgroups give each wave fewer columns, so a chunk takes
-// less time, but a chain then needs more workgroups.
+// the 64-column form's: narrower workgroups give each wave fewer columns, so
+// a chunk takes less time, but a chain then needs more workgroups.  Measured
+// on the MI355X at dk = dv = 128: 1.1 us per chunk at 32 columns with an idle
+// chip, 1.9 us at 64 with every CU busy.  The ratio stands above that of the two
+// because a narrow chain's four workgroups also load the CUs the wide chains
+// wait for: 0.8 to 0.87 give the same widths to the 16-sequence batch (whose
+// longest chains run narrow), a smaller one moves more of it to 32 columns.
 constexpr double kStep32 = 0.87, kStep64 = 1.0;
 
 // Widths of the single-level fused scan for a bf16 call with these
