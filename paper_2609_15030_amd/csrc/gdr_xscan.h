@@ -93,16 +93,34 @@ __device__ __host__ inline int state_row(int x) {
 // between two barriers (iteration i): the scan waves work on chunk i, the
 // output waves on chunk i - 1, and the loaders write chunk i + 1 (Q: chunk i,
 // which only the output waves read).
-template <int DK, int PC, bool OUT> struct XLds {
+template <int DK, int PC, bool OUT> struct XLds;
+
+template <int DK, int PC> struct XLds<DK, PC, true> {
     static constexpr int TW = xscan_tw(PC), NPAIR = xscan_npair(PC), PW = 16 * TW;
     static constexpr int KV = kChunk * DK / 8;   // 16-byte pieces of a chunk's K (or Q)
-    uint4 k[3][KV];                              // K rows, pieces XOR-swizzled by row (xpiece)
-    uint4 q[OUT ? 2 : 1][OUT ? KV : 1];          // Q, same layout
+    static constexpr int KD = 3;                 // chunks of K and gates held
+    uint4 k[KD][KV];                             // K rows, pieces XOR-swizzled by row (xpiece)
+    uint4 q[2][KV];                              // Q, same layout
     uint4 x[2][kXFrags * 64];                    // X diag(beta) fragments
-    float gate[3][kGateBlock];                   // the gate block
+    float gate[KD][kGateBlock];                  // the gate block
     uint4 v[2][NPAIR][kChunk * PW / 8];          // each scan wave's PW value columns, row-major [64][PW]
-    uint4 sbh[OUT ? 2 : 1][OUT ? NPAIR : 1][TW][DK / 32][64]; // S_0 handed to the output waves (B-operand fragments)
-    uint4 ubh[OUT ? 2 : 1][OUT ? NPAIR : 1][TW][2][64];       // U handed to the output waves
+    uint4 sbh[2][NPAIR][TW][DK / 32][64];        // S_0 handed to the output waves (B-operand fragments)
+    uint4 ubh[2][NPAIR][TW][2][64];              // U handed to the output waves
+};
+
+// The maps' LDS: no output waves, so no Q and no hand-offs, and nothing reads
+// chunk i - 1's K.  What it must leave room for is the 64-column maps' other
+// workgroups on the CU (a workgroup has two scan waves for four SIMDs): two in
+// all at dk = 128, three at dk = 64.  32,768 tokens of 16 heads at dk = 128,
+// dv = 64: maps and combine 140 us, against 174 with room for one.
+template <int DK, int PC> struct XLds<DK, PC, false> {
+    static constexpr int TW = xscan_tw(PC), NPAIR = xscan_npair(PC), PW = 16 * TW;
+    static constexpr int KV = kChunk * DK / 8;
+    static constexpr int KD = 2;
+    uint4 k[KD][KV];
+    uint4 x[2][kXFrags * 64];
+    float gate[KD][kGateBlock];
+    uint4 v[2][NPAIR][kChunk * PW / 8];
 };
 
 // LDS of the 128-column form (four scan waves of 32 columns, four output waves
@@ -240,8 +258,9 @@ __device__ __forceinline__ void xscan_run(const ScanArgs &a, XLds<DK, PC, MODE !
     constexpr bool kMix = MODE == kXMap;               // K swizzle key (xpiece)
     constexpr int RT = DK / 16, FS = DK / 4, KS = DK / 32;
     using Lds = XLds<DK, PC, kOut>;
-    constexpr int KV = Lds::KV;
+    constexpr int KV = Lds::KV, KD = Lds::KD;
     static_assert(sizeof(Lds) <= 160 * 1024, "LDS");
+    static_assert(kOut || PC != 64 || (DK == 128 ? 2 : 3) * sizeof(Lds) <= 160 * 1024, "64-column maps share a CU");
     static_assert(!kOut || (NPAIR == 2 && PW * 2 == PC), "two scan waves beside the output waves");
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -325,16 +344,16 @@ __device__ __forceinline__ void xscan_run(const ScanArgs &a, XLds<DK, PC, MODE !
         };
 
         xbar_lds();          // chunk c0's inputs are in LDS
-        int r3 = 0;
+        int rk = 0;          // i % KD
         // The wave issues in order, one instruction every four to five cycles, so
         // its chain is bound by what it issues and by every wait: the LDS reads
         // of a phase are issued among the MFMAs of the phase before
         // (xsched_mix), a few per MFMA, and the MFMAs of a phase go round its
         // accumulators so that none waits for the one before it.
         for (int i = 0; i < nrun; ++i) {
-            const uint4 *K = sm.k[r3];
-            const float *gate = sm.gate[r3];
-            r3 = r3 == 2 ? 0 : r3 + 1;
+            const uint4 *K = sm.k[rk];
+            const float *gate = sm.gate[rk];
+            rk = rk == KD - 1 ? 0 : rk + 1;
             // ---- the previous chunk's state update; this chunk's K fragments
             bf16x8 kf[4][KS];
 #pragma unroll
@@ -618,12 +637,12 @@ __device__ __forceinline__ void xscan_run(const ScanArgs &a, XLds<DK, PC, MODE !
         store_a(st[0], 0, 0);
         load_a(st[0], 2);
         xbar_lds();
-        int slot = 1;          // (i + 1) % 3
+        int slot = 1;          // (i + 1) % KD
         auto iter = [&](auto parity, int i) __attribute__((always_inline)) {
             constexpr int P = decltype(parity)::value;
             store_a(st[P ^ 1], P ^ 1, slot);
             store_q(sq[P], P);
-            slot = slot == 2 ? 0 : slot + 1;
+            slot = slot == KD - 1 ? 0 : slot + 1;
             load_a(st[P ^ 1], i + 3);
             load_q(sq[P], i + 2);
             xbar_lds();
@@ -655,15 +674,15 @@ __device__ __forceinline__ void xscan_run(const ScanArgs &a, XLds<DK, PC, MODE !
                 const int64_t oat = (int64_t)(16 * mt + (NT == 2 ? c16 : c16 & ~1)) * H * DV + vcol0 +
                                     16 * (g16 & 1) + 8 * (g16 >> 1) + (NT == 2 ? 0 : 32 * (c16 & 1));
                 ChunkCursor cur = cur0;
-                int r3 = 0;
+                int rk = 0;
                 for (int j = 0; j < nrun; ++j) {
                     const int lo = cur.pos;
                     cur.advance();
                     const int n = cur.pos - lo;
                     xbar_lds();   // chunk j handed off
-                    const uint4 *K = sm.k[r3], *Q = sm.q[j & 1];
-                    const float *gate = sm.gate[r3];
-                    r3 = r3 == 2 ? 0 : r3 + 1;
+                    const uint4 *K = sm.k[rk], *Q = sm.q[j & 1];
+                    const float *gate = sm.gate[rk];
+                    rk = rk == KD - 1 ? 0 : rk + 1;
                     bf16x8 qf[KS], kk[NK][KS], sb[NT][KS];
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) qf[ks] = row_frag<DK, kMix>(Q, mt, ks, lane);
