@@ -655,10 +655,7 @@ __device__ __forceinline__ void xscan_run(const ScanArgs &a, XLds<DK, PC, MODE !
             iter(std::integral_constant<int, 0>{}, i);
             iter(std::integral_constant<int, 1>{}, i + 1);
         }
-        if (i < nrun) {   // the last of an odd run: only its Q is still to come
-            store_q(sq[0], 0);
-            xbar_lds();
-        }
+        if (i < nrun) iter(std::integral_constant<int, 0>{}, i);
     } else {
         // ================================ output wave ================================
         // One chunk behind the scan waves: chunk j after the barrier that ends

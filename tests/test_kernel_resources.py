@@ -48,11 +48,3 @@ def test_narrow_segment_maps_share_a_cu(kernels, dk, dv, least):
     """A 64-column map workgroup has two scan waves for a CU's four SIMDs: with
     one workgroup per CU half of the SIMDs would run none."""
     assert workgroups_per_cu(kernels[f"gdr_xscan_kernel<{dk}, {dv}, 2, 64>"]) >= least
-
-
-def test_pipelined_scans_keep_everything_in_registers(kernels):
-    """No scratch memory behind the one-barrier scans (32 and 64 columns, the
-    mixed launch, the replay and the maps)."""
-    names = [n for n in kernels if re.match(r"gdr_xscan_(mixed_)?kernel<", n) and not re.search(r", [01], 128>$", n)]
-    assert len(names) == 15
-    assert {n: kernels[n][".private_segment_fixed_size"] for n in names if kernels[n][".private_segment_fixed_size"]} == {}
