@@ -259,25 +259,61 @@ la::ScanArgs scan_args(const PrefillCall &c, const la::Workspace &ws) {
     return sa;
 }
 
-// Per-chunk step of one fused-scan workgroup by column width, relative to
-// the 64-column form's: narrower workgroups give each wave fewer columns, so
-// a chunk takes less time, but a chain then needs more workgroups.  Measured
-// on the MI355X at dk = dv = 128: 1.1 us per chunk at 32 columns with an idle
-// chip, 1.9 us at 64 with every CU busy.  The ratio stands above that of the two
-// because a narrow chain's four workgroups also load the CUs the wide chains
-// wait for: 0.8 to 0.87 give the same widths to the 16-sequence batch (whose
-// longest chains run narrow), a smaller one moves more of it to 32 columns.
-constexpr double kStep32 = 0.87, kStep64 = 1.0;
+// Chunk step of a fused-scan workgroup by column width, in units that make both
+// whole numbers: narrower workgroups give each wave fewer columns, so a chunk
+// takes less time, but a chain then needs more workgroups.  Measured on the
+// MI355X at dk = dv = 128 with a workgroup on every CU (chains of 64 chunks):
+// 1.66 us per chunk at 32 columns, 2.32 at 64, a ratio of 0.72.  In a mix the
+// narrow chains start first and their CUs' next workgroups wait for them, and
+// the ratio that picks well is a little higher: 0.70 to 0.87 are on average
+// within 1.0 to 1.8 % of the best count of narrow chains on 33 batches of 1 to 100
+// sequences (every count measured).
+constexpr int64_t kStep32 = 19, kStep64 = 25;
+constexpr int kXcds = 8, kXcdCUs = (int)kDeviceCUs / kXcds;
+
+// Span of the scan with the n_narrow longest of the ranked chains (nch: their
+// chunks, longest first) in 32-column workgroups and the others in 64-column
+// ones, or limit if it reaches that.  Whole workgroups, in dispatch order, each to
+// the CU that is free first: a CU holds one at a time (130 and 163 KB of LDS).
+// Ranks go round the XCDs, so the XCD of ranks 0, 8, 16, ... has the longest
+// chain of every eight and stands for the others.
+int64_t scan_span(const int64_t *nch, int64_t pairs, int64_t n_narrow, int64_t limit) {
+    int64_t busy[kXcdCUs], span = 0;   // when each CU is free; a min-heap once all are taken
+    int used = 0;
+    for (int64_t rank = 0; rank < pairs; rank += kXcds) {
+        const bool narrow = rank < n_narrow;
+        const int64_t cost = nch[rank] * (narrow ? kStep32 : kStep64);
+        for (int w = narrow ? 4 : 2; w > 0; --w) {
+            if (used < kXcdCUs) {
+                busy[used++] = cost;
+                span = std::max(span, cost);
+                if (used == kXcdCUs) std::make_heap(busy, busy + kXcdCUs, std::greater<int64_t>());
+            } else {
+                const int64_t t = busy[0] + cost;
+                int i = 0;
+                for (int c = 1; c < kXcdCUs; c = 2 * i + 1) {   // the new time sinks from the top
+                    if (c + 1 < kXcdCUs && busy[c + 1] < busy[c]) ++c;
+                    if (busy[c] >= t) break;
+                    busy[i] = busy[c];
+                    i = c;
+                }
+                busy[i] = t;
+                span = std::max(span, t);
+            }
+            if (span >= limit) return limit;
+        }
+    }
+    return span;
+}
 
 // Widths of the single-level fused scan for a bf16 call with these
 // sequence lengths (cu_host valid).  At dk = dv = 128: 128 columns when the
-// chains give every CU two workgroups; else the n_narrow longest chains (a
+// chains are at least two for every CU; else the n_narrow longest chains (a
 // multiple of 8, or all) take 32-column workgroups and the others 64, with
-// n_narrow minimising an estimate of the scan's span: the longest narrow
-// chain, the longest wide chain, or all chunk steps spread over the CUs,
-// whichever is longest (a narrow chain runs four workgroups at kStep32 per
-// chunk, a wide one two at kStep64).  Other head sizes take 64 columns.
-// The widths never change a result.
+// n_narrow minimising the span (scan_span).  Spreading chunk steps over the CUs in
+// fractions instead took all of 9 equal sequences of 8 heads narrow, 288
+// workgroups for 256 CUs: at 4,096 tokens each 175 us, against 120 with all of them
+// wide.  Other head sizes take 64 columns.  The widths never change a result.
 struct ScanWidths {
     int cw;             // 32, 64 or 128; 0 for a mix of 32 (the first n_narrow ranked chains) and 64
     int64_t n_narrow;
@@ -287,33 +323,44 @@ ScanWidths fused_scan_widths(const la_shape *s, const int32_t *cu_host) {
     if (s->dk != 128 || s->dv != 128) return {64, 0};
     if (pairs >= 2 * kDeviceCUs) return {128, 0};
     const int cps = la::chunks_per_interval(s->ckpt_interval);
-    int64_t nch[2 * kDeviceCUs];
-    double total = 0.0;
+    int64_t nch[2 * kDeviceCUs], total = 0;
     for (int64_t k = 0; k < pairs; ++k) {
         const int i = (int)(k / s->n_heads);
         nch[k] = la::n_chunks((int64_t)cu_host[i + 1] - cu_host[i], s->ckpt_interval, cps);
-        total += (double)nch[k];
+        total += nch[k];
     }
     // ranked as the dispatch ranks them (longest first; mixing needs that ranking)
     std::sort(nch, nch + pairs, std::greater<int64_t>());
     const bool can_mix = s->n_seqs >= 2 && pairs <= la::kChainOrderMax;
-    double narrow_sum = 0.0, best = 0.0;
-    int64_t best_k = 0, done = 0;
+    int64_t best = INT64_MAX, best_k = 0, done = 0, narrow_sum = 0;
+    // false once no larger count can be shorter
     auto consider = [&](int64_t k) {
-        for (; done < k; ++done) narrow_sum += (double)nch[done];
-        const double span = std::max({k > 0 ? kStep32 * (double)nch[0] : 0.0,
-                                      k < pairs ? kStep64 * (double)nch[k] : 0.0,
-                                      (4.0 * kStep32 * narrow_sum + 2.0 * kStep64 * (total - narrow_sum)) /
-                                          (double)kDeviceCUs});
-        if (k == 0 || span < best) {
+        for (; done < k; ++done) narrow_sum += nch[done];
+        const int64_t mean = (4 * kStep32 * narrow_sum + 2 * kStep64 * (total - narrow_sum)) / kDeviceCUs;
+        if (mean >= best) return false;   // it grows with the count
+        // no schedule is shorter than its longest chains, than the mean per CU, or,
+        // some CU getting q of the first (q - 1) kXcdCUs + 1 workgroups, than q of
+        // the shortest of those: most counts need no schedule
+        int64_t least = std::max({k > 0 ? kStep32 * nch[0] : 0, k < pairs ? kStep64 * nch[k] : 0, mean});
+        const int64_t narrow = (k + kXcds - 1) / kXcds, all = (pairs + kXcds - 1) / kXcds;
+        for (int64_t q = 2, j = kXcdCUs; j < 2 * (all + narrow); ++q, j += kXcdCUs) {
+            int64_t low = INT64_MAX;
+            if (narrow > 0) low = kStep32 * nch[kXcds * (std::min(j / 4, narrow - 1))];
+            if (j >= 4 * narrow) low = std::min(low, kStep64 * nch[kXcds * (j / 2 - narrow)]);
+            least = std::max(least, q * low);
+        }
+        if (least >= best) return true;
+        const int64_t span = scan_span(nch, pairs, k, best);
+        if (span < best) {
             best = span;
             best_k = k;
         }
+        return true;
     };
-    consider(0);
+    bool more = consider(0);
     if (can_mix)
-        for (int64_t k = 8; k < pairs; k += 8) consider(k);
-    consider(pairs);
+        for (int64_t k = kXcds; more && k < pairs; k += kXcds) more = consider(k);
+    if (more) consider(pairs);
     if (best_k == 0) return {64, 0};
     if (best_k == pairs) return {32, pairs};
     return {0, best_k};
