@@ -367,11 +367,22 @@ ScanWidths fused_scan_widths(const la_shape *s, const int32_t *cu_host) {
 }
 
 // Column width of the two-level passes over `units` (sequence, head,
-// segment) units: 128 while that still gives every CU two workgroups (dk =
-// dv = 128), else 64, which spreads each unit over more CUs.
+// segment) units at dk = dv = 128 (other head sizes: 64).
+// Maps: 64 while each of a unit's four workgroups has a CU to itself; past that
+// two of them share one and take as long as a 128-column one that reads the
+// inputs once.  Maps and combine at 64 | 128 columns, segments of 16 chunks:
+// 64 units 36.2 | 38.5 us, 72 50.3 | 40.6, 128 54.1 | 47.1, 192 76.1 | 74.7,
+// 256 84.6 | 73.6, 512 177 | 157.
+// Replay: a CU holds one workgroup of either width, so units take ceil(units /
+// 128) rounds at 64 columns or ceil(units / 256) rounds 7/4 as long at 128
+// (one round of 16 chunks: 36 and 57 to 65 us).  At 64 | 128 columns: 128 units
+// 37.2 | 56.8 us, 136 63.4 | 57.2, 256 69.2 | 65.3, 272 94.8 | 113, 400 130 | 121,
+// 512 144 | 147, 576 169 | 188, 1,024 303 | 291.
 template <int DK, int DV, int MODE> int two_level_width(int64_t units) {
-    constexpr int NCOLS = MODE == la::kXMap ? DK + DV : DV;
-    return (DK == 128 && DV == 128 && units * (NCOLS / 128) >= 2 * kDeviceCUs) ? 128 : 64;
+    if (DK != 128 || DV != 128) return 64;
+    if (MODE == la::kXMap) return 4 * units > kDeviceCUs ? 128 : 64;
+    const int64_t wide = (units + kDeviceCUs - 1) / kDeviceCUs, narrow = (2 * units + kDeviceCUs - 1) / kDeviceCUs;
+    return 7 * wide < 4 * narrow ? 128 : 64;
 }
 
 // The fused scan kernel of one mode over `units` independent units at

@@ -1,6 +1,7 @@
-"""The narrow count of the fused scan's mixed launch, against a schedule of
-whole workgroups: in dispatch order, each to the compute unit of its XCD that is
-free first, one workgroup per unit (two do not fit its LDS)."""
+"""Column widths of the fused scan: the narrow count of its mixed launch,
+against a schedule of whole workgroups (in dispatch order, each to the compute
+unit of its XCD that is free first, one workgroup per unit: two do not fit its
+LDS), and the widths of the two-level passes."""
 import heapq
 
 import numpy as np
@@ -56,3 +57,35 @@ def test_chosen_count_is_near_the_best_schedule():
         counts = [0, len(chains)] + (list(range(8, len(chains), 8)) if n > 1 else [])
         best = min(span(chains, k) for k in counts)
         assert span(chains, narrow) <= 1.03 * best, (lens.tolist(), H, C, narrow)
+
+
+@pytest.mark.parametrize("segments,width", [(1, 64), (16, 64), (17, 128), (32, 128), (34, 64), (48, 64), (50, 128),
+                                            (64, 128), (72, 64), (82, 128)])
+def test_replay_width_follows_the_rounds(segments, width):
+    """The two-level replay (one workgroup per compute unit at 64 and at 128
+    columns): the width whose rounds over 8 heads x segments are shorter."""
+    shape = la.make_shape(1, 8, 128, 128, 1024, la.LA_BF16)
+    assert la.la_prefill_scan_columns(shape, np.array([0, 1024 * segments], np.int32)) == (width, 0)
+
+
+@pytest.mark.gpu
+def test_two_level_widths_give_the_same_bits():
+    """8,704 tokens of 8 heads at C = 512 (136 units: maps and replay at 128
+    columns) against the oracle, and resumed at 4,608 (64 units: both at 64) and
+    at 4,096 (72: maps at 128, replay at 64) with the cold run's bits."""
+    import torch
+
+    from paper_2609_15030_amd import api
+    from paper_2609_15030_amd import workloads as wl
+    from parity import TOL, compare, oracle_run
+    N, C = 8704, 512
+    x = wl.random_inputs(77, [N], 8, 128, 128, wl.BF16, gate_scale=0.02)
+    res = api.prefill(api.to_device(x), C)
+    torch.cuda.synchronize()
+    compare(res, oracle_run(x, interval=C), x.cu_seqlens, TOL[la.LA_BF16], "two-level widths")
+    for B in (4608, 4096):
+        row = B // C - 1
+        r2 = api.prefill_resume(api.to_device(x.tokens(B, N)), [B], res.ckpt[row:row + 1].clone(), C)
+        torch.cuda.synchronize()
+        assert torch.equal(r2.o, res.o[B:]) and torch.equal(r2.final_state, res.final_state)
+        assert torch.equal(r2.ckpt, res.ckpt[row + 1:])
