@@ -195,12 +195,12 @@ __device__ __host__ inline int64_t total_slots(int64_t total_tokens, int64_t n_s
 //     slot_base), for every head, go to XCD t % 8, so the chunk's gates and
 //     betas (stored [token, head]: a cache line holds a few tokens of every
 //     head) are fetched once into one L2 rather than once per head into
-//     several; block id = 8 * ((t / 8) * H + head) + t % 8.  Slots exist for the
-//     chunks there are (one spare per sequence at most), so a batch of uneven or
-//     short sequences launches no blocks for chunks it does not have and
-//     loads all XCDs alike: with a slot per (sequence, chunk number) instead, 64
-//     prompts of 1 to 300 tokens used five XCDs of eight (26 us for the
-//     preparation).
+//     several; block id = 8 * ((t / 8) * H + head) + t % 8.  Slots follow the
+//     chunks there are (at most one spare per sequence, two when C is above 64 and
+//     no multiple of it; the blocks of spare slots leave at once), so a batch of
+//     uneven or short sequences loads all XCDs alike: with a block per (sequence,
+//     chunk number) instead, 64 prompts of 1 to 300 tokens used five XCDs of eight
+//     (26 us for the preparation, 15 by slots).
 // The host takes slot-major for launches of many units, where the gathers'
 // traffic counts, and pair-major otherwise.
 // ---------------------------------------------------------------------------
@@ -265,8 +265,11 @@ __device__ inline bool unit_of_block(const UnitMap &u, const int32_t *cu, int *s
     return true;
 }
 
-// Blocks of a launch over every (sequence, head, chunk number), the bound a
-// call is checked against, and blocks of the launch itself.
+// Blocks of a slot-major launch, and of a launch over every (sequence, head,
+// chunk number).  A call is refused when either exceeds a grid: spare slots
+// can make the first the larger one.
+__host__ inline int64_t slot_grid_blocks(int64_t slots, int n_heads) { return 8 * ((slots + 7) / 8) * n_heads; }
+
 __host__ inline int64_t chunk_grid_blocks(int n_seqs, int n_heads, int64_t max_chunks) {
     if (slot_major_map(n_seqs, n_heads, max_chunks)) return 8 * ((max_chunks + 7) / 8) * (int64_t)n_seqs * n_heads;
     return 8 * max_chunks * (((int64_t)n_seqs * n_heads + 7) / 8);
@@ -279,7 +282,7 @@ __host__ inline UnitMap unit_map(int n_seqs, int n_heads, int C, int cps, int64_
 }
 
 __host__ inline int64_t unit_map_blocks(const UnitMap &u) {
-    if (u.slots > 0) return 8 * (((int64_t)u.slots + 7) / 8) * u.n_heads;
+    if (u.slots > 0) return slot_grid_blocks(u.slots, u.n_heads);
     return chunk_grid_blocks(u.n_seqs, u.n_heads, u.max_chunks);
 }
 

@@ -593,8 +593,8 @@ la_status run_prefill(const PrefillCall &c) {
             if (B > ((int64_t)1 << 40)) return fail(LA_ERR_INVALID_ARG, "start_pos[%d] too large", i);
         }
     }
-    if (max_chunks > 0x7fffffff ||
-        la::chunk_grid_blocks(s->n_seqs, s->n_heads, max_chunks) > 0x7fffffff)
+    if (max_chunks > 0x7fffffff || la::chunk_grid_blocks(s->n_seqs, s->n_heads, max_chunks) > 0x7fffffff ||
+        la::slot_grid_blocks(la::total_slots(total, s->n_seqs, C, cps), s->n_heads) > 0x7fffffff)
         return fail(LA_ERR_INVALID_ARG, "sequence too long for one launch");
     {
         const int m = seg_chunks(s);

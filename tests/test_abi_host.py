@@ -146,6 +146,24 @@ def test_resume_state_validation_before_launch():
     assert call(state_in=FAKE + 4) == la.LA_ERR_INVALID_ARG              # misaligned state
 
 
+def test_slot_numbered_grid_is_bounded_before_launch():
+    """Chunk kernels numbered by workspace slot launch spare slots' blocks too:
+    386 tokens at C = 129 are 8 chunks in almost 10 slots.  A call whose slots
+    exceed a grid is refused although its chunks would not (no workspace is
+    passed, so nothing can launch)."""
+    n, H, C = 3700, 65535, 129
+    cu = np.arange(n + 1, dtype=np.int32) * 386
+    assert 8 * n * H <= 0x7fffffff
+    P = la.ctypes.c_void_p(cu.ctypes.data)
+    for io in (la.LA_BF16, la.LA_F32):
+        sh = la.make_shape(n, H, 64, 64, C, io)
+        call = lambda: la.library().la_prefill(la.ctypes.byref(sh), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, P, FAKE, None,
+                                               None, None, None, None, 0, None)
+        assert call() == la.LA_ERR_INVALID_ARG and "too long for one launch" in la.last_error_message()
+    sh = la.make_shape(n // 2, H, 64, 64, C)              # within the bound: refused for its workspace
+    assert call() == la.LA_ERR_WORKSPACE
+
+
 def test_prefill_form_is_a_function_of_the_shape():
     """The kernels a call runs depend on dtype, head dims and C only (never
     on lengths), so a resume runs the arithmetic of the run that wrote its
