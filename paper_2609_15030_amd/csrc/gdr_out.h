@@ -13,8 +13,7 @@
 // operand of X, including the contraction-index permutation perm_row), Q^T
 // and P^T are B operands (both written by the preparation kernel in that
 // order, read here with whole 16-byte vectors), and each lane ends with 4
-// consecutive output columns of one token: one 8-byte (bf16) or 16-byte
-// (fp32) store.
+// consecutive output columns of one token: 16 bytes.
 //
 // The scan kernel's output wave and the split output kernel run this same
 // code on the same operands, so both paths produce identical bits.
@@ -38,14 +37,6 @@ template <typename T, int DK, int NMT> struct OutFrag {
     T p[NMT][FU];
     float eg[4];
 };
-
-template <typename T> __device__ inline void buf_store_4(__amdgpu_buffer_rsrc_t r, uint32_t voff, const T *src);
-template <> __device__ inline void buf_store_4<__bf16>(__amdgpu_buffer_rsrc_t r, uint32_t voff, const __bf16 *src) {
-    buf_store8(*(const uint2 *)src, r, voff, 0u);
-}
-template <> __device__ inline void buf_store_4<float>(__amdgpu_buffer_rsrc_t r, uint32_t voff, const float *src) {
-    buf_store16(*(const uint4 *)src, r, voff, 0u);
-}
 
 // Byte range of rows [0, n) of one head in a [tokens, H, D] tensor, counted
 // from row 0 of that head: row n and later fall outside it, so buffer
@@ -109,7 +100,7 @@ __device__ inline void out_tile(const OutFrag<T, DK, NMT> &f, const T *sb, const
         for (int i = 0; i < 4; ++i) out[i] = from_f32<T>(acc[i] * scale);
         const uint32_t voff = ((uint32_t)(16 * mt + c16) * (uint32_t)(H * DV) + (uint32_t)(16 * tile + 4 * g16)) *
                               (uint32_t)sizeof(T);
-        buf_store_4<T>(ro, voff, out);
+        buf_store16(*(const uint4 *)out, ro, voff, 0u);
     }
 }
 

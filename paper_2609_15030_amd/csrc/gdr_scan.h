@@ -177,7 +177,7 @@ struct CkptDst {
 };
 
 // Chunk bounds of one sequence, advanced by additions only (the plan of
-// chunk_range without a division per chunk).  All counters are 32-bit:
+// chunk_range32 without a division per chunk).  All counters are 32-bit:
 // sequence lengths and C are below 2^31, and 64-bit compares in the loop
 // would need vector temporaries that alias in-flight operand loads.
 struct ChunkCursor {
@@ -211,14 +211,6 @@ __device__ inline void store_state_tiles(float *dst, const f32x4 (&S)[NTILE], ui
 // State tiles in C layout ([tile][row tile][lane] of f32x4): the two-level
 // scan's segment-entering states, written by the combine and read by the
 // replay (one 16-byte access per row tile and lane).
-template <int RT>
-__device__ inline void store_state_c(float *base, int tile, const f32x4 (&S)[RT]) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-        ((float4 *)base)[(tile * RT + t) * 64 + lane] = make_float4(S[t][0], S[t][1], S[t][2], S[t][3]);
-}
-
 template <int RT>
 __device__ inline void load_state_c(const float *base, int tile, f32x4 (&S)[RT]) {
     const int lane = threadIdx.x & 63;
@@ -336,7 +328,7 @@ __global__ __launch_bounds__(64 * (DK / 32)) void gdr_scan_kernel(ScanArgs a) {
         const auto ru = make_rsrc((const T *)a.ws.ut + sh * L::ut_elems, L::ut_elems * sizeof(T));
 #pragma unroll
         for (int m = 0; m < MTW; ++m)
-            if (w * MTW + m < NMT) o.ut[m] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + w * MTW + m));
+            if (w * MTW + m < NMT) o.ut[m] = load_ut(ru, (uint32_t)lane, (uint32_t)(tile * 4 + w * MTW + m));
         const auto rw = make_rsrc((const T *)a.ws.w + sh * L::w_elems, L::w_elems * sizeof(T));
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt)
@@ -495,7 +487,7 @@ __device__ inline void scan1_chunks(const ScanArgs &a, int seq, int h, int tile,
         o.ckid = ck.load_id(jj / a.cps);
         const auto ru = make_rsrc((const T *)a.ws.ut + sh * L::ut_elems, L::ut_elems * sizeof(T));
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) o.ut[mt] = load_ut<T>(ru, (uint32_t)lane, (uint32_t)(tile * 4 + mt));
+        for (int mt = 0; mt < NMT; ++mt) o.ut[mt] = load_ut(ru, (uint32_t)lane, (uint32_t)(tile * 4 + mt));
         const auto rw = make_rsrc((const T *)a.ws.w + sh * L::w_elems, L::w_elems * sizeof(T));
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt)

@@ -34,12 +34,6 @@ template <> struct MT<__bf16> {
     }
     // 8 consecutive values; v must be 16-byte aligned.
     __device__ static inline frag pack(const __bf16 *v) { return *(const frag *)v; }
-    // Two runs of 4 consecutive values (8-byte aligned each).
-    __device__ static inline frag pack2(const __bf16 *lo, const __bf16 *hi) {
-        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-        const bf16x4 a = *(const bf16x4 *)lo, b = *(const bf16x4 *)hi;
-        return frag{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    }
 };
 
 template <> struct MT<float> {
@@ -50,7 +44,6 @@ template <> struct MT<float> {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
     __device__ static inline frag pack(const float *v) { return v[0]; }
-    __device__ static inline frag pack2(const float *lo, const float *) { return lo[0]; }
 };
 
 // Raw buffer access: a scalar resource (base, size) plus a per-lane byte
@@ -81,18 +74,6 @@ __device__ inline void buf_store16(uint4 x, __amdgpu_buffer_rsrc_t r, uint32_t v
     __builtin_amdgcn_raw_buffer_store_b64(lo, r, (int)voff, (int)soff, 0);
     __asm__ volatile("" ::: "memory");
     __builtin_amdgcn_raw_buffer_store_b64(hi, r, (int)(voff + 8u), (int)soff, 0);
-}
-
-__device__ inline uint2 buf_load8(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    typedef int i32x2 __attribute__((ext_vector_type(2)));
-    const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
-    return make_uint2((uint32_t)v[0], (uint32_t)v[1]);
-}
-
-__device__ inline void buf_store8(uint2 x, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    typedef int i32x2 __attribute__((ext_vector_type(2)));
-    const i32x2 v = {(int)x.x, (int)x.y};
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)voff, (int)soff, 0);
 }
 
 __device__ inline float buf_load4f(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
@@ -135,18 +116,6 @@ __device__ __host__ inline int64_t n_chunks(int64_t len, int64_t C, int cps) {
     return full * cps + (rem + kChunk - 1) / kChunk;
 }
 
-// Local token range [a, b) of chunk j.
-__device__ __host__ inline void chunk_range(int64_t j, int64_t len, int64_t C, int cps,
-                                            int64_t *a, int64_t *b) {
-    const int64_t seg = j / cps, sub = j % cps;
-    const int64_t lo = seg * C + (int64_t)sub * kChunk;
-    int64_t hi = lo + kChunk;
-    if (hi > (seg + 1) * C) hi = (seg + 1) * C;
-    if (hi > len) hi = len;
-    *a = lo;
-    *b = hi;
-}
-
 // 32-bit forms for device code (sequence lengths and C are below 2^31; the
 // host validates that), which avoid 64-bit integer division.
 __device__ inline int n_chunks32(int len, int C, int cps) {
@@ -154,6 +123,7 @@ __device__ inline int n_chunks32(int len, int C, int cps) {
     return full * cps + (rem + kChunk - 1) / kChunk;
 }
 
+// Local token range [a, b) of chunk j.
 __device__ inline void chunk_range32(int j, int len, int C, int cps, int *a, int *b) {
     const int seg = j / cps, sub = j - seg * cps;
     const int lo = seg * C + sub * kChunk;
@@ -309,18 +279,10 @@ struct Workspace {
 
 // U~ tile vector `vec` (= column tile * 4 + row tile) of one slot-head, as
 // lane `lane` holds it in the C layout (rows 4 (lane / 16) + i, column
-// lane % 16): four consecutive elements of the io type, widened to fp32 as
-// the accumulator of U = U~ - W S.
-template <typename T>
+// lane % 16): four consecutive elements, the accumulator of U = U~ - W S.
 __device__ inline f32x4 load_ut(__amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t vec) {
-    if constexpr (sizeof(T) == 4) {
-        const uint4 x = buf_load16(r, 16u * lane, 1024u * vec);
-        return f32x4{__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w)};
-    } else {
-        const uint2 x = buf_load8(r, 8u * lane, 512u * vec);
-        return f32x4{__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xffff0000u), __uint_as_float(x.y << 16),
-                     __uint_as_float(x.y & 0xffff0000u)};
-    }
+    const uint4 x = buf_load16(r, 16u * lane, 1024u * vec);
+    return f32x4{__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w)};
 }
 
 template <typename T, int DK, int DV> struct WsLayout {
