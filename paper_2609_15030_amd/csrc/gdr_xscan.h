@@ -34,7 +34,7 @@
 // rest is LDS and memory traffic of the other roles.  With two barriers per chunk
 // and an output wave per scan wave (the form the 128-column workgroups keep,
 // xscan_wide_run) 3,584 tokens of 8 heads took 75 us (now 63), the 16-sequence
-// batch 198 (now 177) and the 32K prompt's maps 122 (now 104).
+// batch 198 (now 184) and the 32K prompt's maps 122 (now 107).
 //
 // Loads: buffer loads into registers while earlier chunks are computed, rows
 // past a chunk's end reading as zero through the buffer range, then LDS
