@@ -313,7 +313,9 @@ int64_t scan_span(const int64_t *nch, int64_t pairs, int64_t n_narrow, int64_t l
 // n_narrow minimising the span (scan_span).  Spreading chunk steps over the CUs in
 // fractions instead took all of 9 equal sequences of 8 heads narrow, 288
 // workgroups for 256 CUs: at 4,096 tokens each 175 us, against 120 with all of them
-// wide.  Other head sizes take 64 columns.  The widths never change a result.
+// wide.  128 columns against the best mix: 256 even chains of 16 chunks 75.6 and
+// 77.7 us, 264 uneven ones 74 and 50, 320 of two chunks 26.1 and 24.8, 512 ragged
+// ones 36 and 54.  Other head sizes take 64 columns.  The widths never change a result.
 struct ScanWidths {
     int cw;             // 32, 64 or 128; 0 for a mix of 32 (the first n_narrow ranked chains) and 64
     int64_t n_narrow;
